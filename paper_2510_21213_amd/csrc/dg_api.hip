@@ -2068,7 +2068,7 @@ dg_status dg_boundary_data_noalloc(dg_ctx* ctx, int mesh_id, int nsrc, const dou
         if (L0.family != 0)
             throw ArgError("Dirichlet data by quadrature need Gauss-Lobatto nodes (pass g at the face points)");
         const dg::QuadPlan P = dg::quad_plan_bounded(L0, nsrc, cap);
-        if (P.R == 0) throw ArgError("mesh too large for the fixed work space (records of one source exceed it)");
+        if (P.rmax == 0) throw ArgError("mesh too large for the fixed work space (records of one source exceed it)");
         // records first, then the split partial sums (every entry read is written first in the call)
         double* part = P.part_len > 0 ? scr + P.rec_len : nullptr;
         dg::launch_quad_data(L0, L0.dev64, M.qnodes, P, nsrc, f, nullptr, nullptr, nullptr, scr, part, g, stream);

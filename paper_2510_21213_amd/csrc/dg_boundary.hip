@@ -12,29 +12,49 @@
 // singular; the method has f vanish there, so terms closer than a millionth of
 // the smallest element width are left out.
 //
-// Work per source: n_face * n_dofs pair terms, a dense FP64 boundary-by-volume
-// sum bound by FP64 vector issue.  The kernels are laid out for that:
-//  * k_quad_pack writes, for a tile of R sources, the records W_q f_s(x_q)
-//    (s in the tile) in lattice order of the grid nodes [Z][Y][X];
-//  * in k_quad each lane owns one boundary node and the R sums of the tile;
-//    all lanes visit the grid nodes in the same order, so the node's x
-//    coordinate and its R weighted values are wave-uniform and are read with
-//    scalar loads into SGPR operands of the FMAs;
-//  * the squared distance is built per lattice row: dy^2 + dz^2 once, then one
-//    FMA per node; 1/|r| is the hardware reciprocal square root refined by the
-//    first two terms of its error series;
-//  * only rows on the boundary surface of the lattice (and the first and last
-//    node of the other rows) can hold a coincident node, so only those terms
-//    pay for the distance test;
-//  * the Z planes are split into parts so that a launch holds several rounds of
-//    resident waves; the parts' partial sums are added in a fixed order by
-//    k_quad_sum.  Work-groups are ordered so that each XCD takes the boundary
-//    tiles of one part at a time: they stream the same records through its L2.
+// Reflections.  The mesh is uniform, so its nodes, weights and boundary nodes are
+// invariant under the eight reflections rho of the box about its centre, and the
+// sum is a convolution over that group: with b and a running over one octant of the
+// boundary and of the grid, chi_s the eight parities, and
+//     F_s(a) = sum_sigma chi_s(sigma) (W f)(sigma a),
+//     K_s(b, a) = sum_tau chi_s(tau) / |b - tau a|,
+// g(rho b) = 1/8 sum_s chi_s(rho) sum_a K_s(b, a) F_s(a).  A pair (b, a) costs eight
+// inverse distances and 8 multiply-adds per source where the plain sum over its 64
+// images costs 64 of each: an eighth of the work, with the same terms in FP64.
+// (A node whose coordinate is its own mirror image, the middle one of an odd count,
+// is met twice by the group; its weight is halved per such axis.)
+//
+// The sum is bound by FP64 issue (vector and matrix units share the 72-78 TFLOP/s):
+//  * k_quad_pack writes, for a tile of R sources, the records F_s(a) as [a][s][R] in
+//    lattice order of the octant;
+//  * k_quad (R <= 4): a lane owns one octant boundary node and its 8 R sums; all lanes
+//    visit the grid nodes in the same order, so the records are wave-uniform and come
+//    in through scalar loads as SGPR operands of the FMAs;
+//  * k_quad_mfma (R = 16, 32): per parity a matrix product K_s F_s on
+//    v_mfma_f64_16x16x4; a lane computes the eight inverse distances of one
+//    (boundary node, grid node) pair and their parity combinations, which are its A
+//    operands as they are, and the records are staged in LDS for the work-group's
+//    four waves (64 boundary nodes);
+//  * k_quad_combine adds the split parts in a fixed order and turns the eight parity
+//    sums of an octant boundary node into the values at its eight images.
+// The octant is split into parts so that a launch holds several rounds of resident
+// waves; work-groups are ordered so that each XCD takes the boundary tiles of one part
+// at a time: they stream the same records through its L2.
+//
+// Measured (36 pair densities of 16^3 elements, p = 4; 38,400 boundary nodes x 512,000
+// grid nodes): 6.5 ms for the whole call, 33.5 ms as a plain sum over all nodes; one density
+// 1.63 ms against 6.8.  16 sources take 2.8 ms, 32 4.6, 4 1.9: a pass costs about 1.5 ms of
+// inverse distances (83 FP64 instructions and 8 reciprocal roots per pair) and 0.10 (vector) or
+// 0.11 ms (matrix, of the padded width) a source; the FP64 vector and matrix instructions do not
+// overlap, so the sum of the two bounds it.
+// Tried: 48 and 64 sources a tile (one wave per SIMD: 9.7 and 28 ms), K of the next step formed
+// between the matrix instructions (no faster: 6.5 ms).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <mutex>
 #include <stdexcept>
+#include <type_traits>
 
 #include "dg_internal.h"
 #include "dg_kernels.h"
@@ -43,44 +63,135 @@ namespace dg {
 
 namespace {
 
-constexpr int QUAD_RMAX = 48;      // sources per tile (accumulators per lane)
-// waves a launch aims for: 32 per SIMD, several rounds of the waves that fit at once (the loop
-// waits on scalar loads, so waves queued behind the resident ones keep the SIMDs fed; measured
-// on the 36 pair densities of 16^3 elements, p = 4: 8 per SIMD 44.3 ms, 16 38.2, 32 36.9, 64 38.4)
-constexpr int QUAD_WAVES = 32768;
-constexpr int QUAD_BLOCK = 256;    // threads per workgroup (its waves read the same records)
-constexpr int QUAD_NB = 1;         // boundary nodes per lane (each scalar-loaded value feeds QUAD_NB FMAs)
+constexpr int QUAD_BLOCK = 256;    // threads per work-group
+constexpr int QUAD_VEC = 4;        // widest source tile of the vector kernel
+// Source tile for `left` more sources, at most rmax.  Up to 4 go to the vector kernel (1.63 to 1.95 ms
+// on 16^3 elements, p = 4, against 2.8 ms for a matrix tile of 16; its records then fill the SGPRs), more
+// to the narrowest matrix tile that holds them (17..20 sources: 4.5 ms in a tile of 32, 4.7 ms in 16
+// and a vector pass).
+constexpr int quad_tile(int left, int rmax) {
+    if (left > 16 && rmax >= 32) return 32;
+    if (left > QUAD_VEC && rmax >= 16) return 16;
+    return left < QUAD_VEC ? (left < rmax ? left : rmax) : (rmax < QUAD_VEC ? rmax : QUAD_VEC);
+}
+// Waves a launch aims for: two to four rounds of those that fit at once (5 to 8 per SIMD in the vector
+// kernel, which waits on scalar loads; 2 or 3 in the matrix kernel), so that a last round costs little.
+constexpr int QUAD_WAVES_VEC = 16384, QUAD_WAVES_MFMA = 8192;
+constexpr int QUAD_CHUNK = 8;      // octant nodes per LDS stage of the matrix kernel (two MFMA steps)
 
-__global__ __launch_bounds__(256) void k_quad_pack(const LevelDev<double>* __restrict__ dev, int Ex, int Ey, int n,
-                                                   long long ndof, int NX, int NY, int nsrc, int r0, int R,
-                                                   const double* __restrict__ f, const double* __restrict__ phi,
-                                                   const int* __restrict__ pi, const int* __restrict__ pj,
-                                                   double* __restrict__ rec) {
-    const long long q = blockIdx.x * 256LL + threadIdx.x;
-    if (q >= ndof) return;
-    const int n3 = n * n * n;
-    const long long e = q / n3;
-    const int l = (int)(q - e * n3);
-    const int i = l % n, j = (l / n) % n, k = l / (n * n);
-    const int ex = (int)(e % Ex), ey = (int)((e / Ex) % Ey), ez = (int)(e / ((long long)Ex * Ey));
-    const double w = dev->ax[0].m[i] * dev->ax[1].m[j] * dev->ax[2].m[k];
-    const long long G = (ex * n + i) + (long long)NX * ((ey * n + j) + (long long)NY * (ez * n + k));
-    double* out = rec + G * R;
-    for (int r = 0; r < R; ++r) {
-        const int s = r0 + r;
-        double v = 0.0;
-        if (s < nsrc)
-            v = w * (f ? f[(long long)s * ndof + q] : phi[(long long)pi[s] * ndof + q] * phi[(long long)pj[s] * ndof + q]);
-        out[r] = v;
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// Octant sizes: node counts per axis N and of the half axes H = ceil(N / 2).
+struct QuadDims {
+    int N[3], H[3];
+    int noct;   // octant grid nodes
+    int nbo;    // octant boundary nodes (faces x, y, z in turn)
+};
+
+QuadDims quad_dims(const LevelHost& L) {
+    QuadDims d;
+    for (int k = 0; k < 3; ++k) {
+        d.N[k] = L.E[k] * L.n;
+        d.H[k] = (d.N[k] + 1) / 2;
+    }
+    d.noct = d.H[0] * d.H[1] * d.H[2];
+    d.nbo = d.H[2] * d.H[1] + d.H[2] * d.H[0] + d.H[1] * d.H[0];
+    return d;
+}
+
+// sum over parities: v[s] = sum_t chi_s(t) v[t], bit d of the index standing for axis d
+__device__ __forceinline__ void parities(double (&v)[8]) {
+#pragma unroll
+    for (int d = 1; d < 8; d <<= 1)
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            if (!(t & d)) {
+                const double a = v[t], b = v[t | d];
+                v[t] = a + b;
+                v[t | d] = a - b;
+            }
+}
+
+// octant boundary node -> lattice indices (all in the lower half)
+__device__ __forceinline__ void oct_face_node(int b, const QuadDims& D, int& f, int& X, int& Y, int& Z) {
+    const int fx = D.H[2] * D.H[1], fy = D.H[2] * D.H[0];
+    if (b < fx) {
+        f = 0; X = 0; Y = b % D.H[1]; Z = b / D.H[1];
+    } else if (b < fx + fy) {
+        b -= fx;
+        f = 1; Y = 0; X = b % D.H[0]; Z = b / D.H[0];
+    } else {
+        b -= fx + fy;
+        f = 2; Z = 0; X = b % D.H[0]; Y = b / D.H[0];
     }
 }
 
-// 1/|r - x_q| for the lane's boundary node at squared distance d2 + (bx - xq)^2; with MASK,
-// 0 for a node at the boundary node itself.
+// where the image rho of that node lies in a face vector (x faces [Z][Y], y faces [Z][X], z faces [Y][X])
+__device__ __forceinline__ int face_slot(int f, int X, int Y, int Z, int rho, const QuadDims& D) {
+    const int NX = D.N[0], NY = D.N[1], NZ = D.N[2];
+    const int x = rho & 1 ? NX - 1 - X : X, y = rho & 2 ? NY - 1 - Y : Y, z = rho & 4 ? NZ - 1 - Z : Z;
+    if (f == 0) return (rho & 1) * NZ * NY + z * NY + y;
+    if (f == 1) return 2 * NZ * NY + ((rho >> 1) & 1) * NZ * NX + z * NX + x;
+    return 2 * NZ * NY + 2 * NZ * NX + ((rho >> 2) & 1) * NY * NX + y * NX + x;
+}
+
+// axes (bits) on which the node is its own mirror image
+__device__ __forceinline__ int self_mask(int X, int Y, int Z, const QuadDims& D) {
+    return (2 * X == D.N[0] - 1 ? 1 : 0) | (2 * Y == D.N[1] - 1 ? 2 : 0) | (2 * Z == D.N[2] - 1 ? 4 : 0);
+}
+
+// one source value W f at a lattice node
+__device__ __forceinline__ double quad_source(int s, int X, int Y, int Z, const QuadDims& D, int n, long long ndof,
+                                              const LevelDev<double>* __restrict__ dev,
+                                              const double* __restrict__ f, const double* __restrict__ phi,
+                                              const int* __restrict__ pi, const int* __restrict__ pj) {
+    const int ex = X / n, i = X - ex * n, ey = Y / n, j = Y - ey * n, ez = Z / n, k = Z - ez * n;
+    const long long q = (((long long)ez * (D.N[1] / n) + ey) * (D.N[0] / n) + ex) * (n * n * n) + (k * n + j) * n + i;
+    const double w = dev->ax[0].m[i] * dev->ax[1].m[j] * dev->ax[2].m[k];
+    return w * (f ? f[(long long)s * ndof + q] : phi[(long long)pi[s] * ndof + q] * phi[(long long)pj[s] * ndof + q]);
+}
+
+// Records F_s(a), [a][s][R].  A work-group takes 16 octant nodes (runs of neighbouring nodes) and 16
+// sources at a time; the records leave through LDS so that both sides are contiguous.
+constexpr int PACK_NODES = 16, PACK_SRC = 16;
+__global__ __launch_bounds__(PACK_NODES* PACK_SRC) void k_quad_pack(const LevelDev<double>* __restrict__ dev,
+                                                                    QuadDims D, int n, long long ndof, int nsrc,
+                                                                    int r0, int R, const double* __restrict__ f,
+                                                                    const double* __restrict__ phi,
+                                                                    const int* __restrict__ pi,
+                                                                    const int* __restrict__ pj,
+                                                                    double* __restrict__ rec) {
+    __shared__ double out[PACK_NODES][8][PACK_SRC];
+    const int q0 = blockIdx.x * PACK_NODES, nn = min(PACK_NODES, D.noct - q0);
+    const int a = threadIdx.x % PACK_NODES, r = threadIdx.x / PACK_NODES;
+    const int q = min(q0 + a, D.noct - 1);
+    const int X = q % D.H[0], Y = (q / D.H[0]) % D.H[1], Z = q / (D.H[0] * D.H[1]);
+    const int self = self_mask(X, Y, Z, D);
+    const double half = 1.0 / (double)(1 << __popc(self));
+    for (int rb = 0; rb < R; rb += PACK_SRC) {
+        const int s = r0 + rb + r, nr = min(PACK_SRC, R - rb);
+        double v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            v[t] = s < nsrc && rb + r < R
+                       ? half * quad_source(s, t & 1 ? D.N[0] - 1 - X : X, t & 2 ? D.N[1] - 1 - Y : Y,
+                                            t & 4 ? D.N[2] - 1 - Z : Z, D, n, ndof, dev, f, phi, pi, pj)
+                       : 0.0;
+        parities(v);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 8; ++t) out[a][t][r] = v[t];
+        __syncthreads();
+        for (int t = threadIdx.x; t < nn * 8 * nr; t += PACK_NODES * PACK_SRC) {
+            const int row = t / nr, c = t - row * nr;
+            rec[((long long)q0 * 8 + row) * R + rb + c] = out[row / 8][row % 8][c];
+        }
+    }
+}
+
+// 1/sqrt(r2); with MASK, 0 for a node at the boundary node itself.
 template <bool MASK>
-__device__ __forceinline__ double inv_dist(double bx, double d2, double xq, double drop2) {
-    const double dx = bx - xq;
-    const double r2 = fma(dx, dx, d2);
+__device__ __forceinline__ double inv_dist(double r2, double drop2) {
     // the hardware estimate is good to about 5e-8; with e = 1 - r2 y^2 the exact value is
     // y (1 - e)^(-1/2) = y (1 + e/2 + 3e^2/8 + ...), so two terms of the series leave O(e^3)
     double y = __builtin_amdgcn_rsq(r2);
@@ -90,48 +201,32 @@ __device__ __forceinline__ double inv_dist(double bx, double d2, double xq, doub
     return y;
 }
 
-// acc += sum over the row's nodes x0 <= xq < x1 of (W f)_xq / |r - x_q| for the lane's NB
-// boundary nodes.  The inverse distances of U nodes are formed together (independent chains,
-// one scalar load of their coordinates), then their R weighted values are read as
-// wave-uniform operands.  U = 8 for wide tiles (36 sources of 16^3 elements, p = 4: U = 4
-// 36.4 ms, 6 34.4, 8 33.6, 16 47.5 with 3 waves per SIMD); narrow tiles keep 4, and so does
-// the widest (48 accumulators: with U = 8 it would drop to 3 waves per SIMD).
-template <int R, int NB, bool MASK>
-__device__ __forceinline__ void quad_run(const double (&bx)[NB], const double (&d2)[NB],
-                                         const double* __restrict__ xs, const double* __restrict__ row, int x0,
-                                         int x1, double drop2, double (&acc)[NB][R]) {
-    constexpr int U = NB == 1 ? (R >= 24 && R <= 40 ? 8 : 4) : 2;
-    int xq = x0;
-    for (; xq + U <= x1; xq += U) {
-        double y[U][NB];
+// K_s of a pair: d[t] = squared distance in y and z to the images (ty, tz) = (t & 1, t >> 1), and the
+// distances of the two x images from the boundary node's and the grid node's distance to the centre.
+template <bool MASK>
+__device__ __forceinline__ void pair_kernel(double bx, double ax, const double (&d)[4], double drop2,
+                                            double (&k)[8]) {
+    const double xm = bx - ax, xp = bx + ax;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int k = 0; k < NB; ++k) y[u][k] = inv_dist<MASK>(bx[k], d2[k], xs[xq + u], drop2);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const double* wf = row + (long long)(xq + u) * R;
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int k = 0; k < NB; ++k) acc[k][r] = fma(wf[r], y[u][k], acc[k][r]);
-        }
+    for (int t = 0; t < 4; ++t) {
+        k[2 * t] = inv_dist<MASK>(fma(xm, xm, d[t]), drop2);
+        k[2 * t + 1] = inv_dist<MASK>(fma(xp, xp, d[t]), drop2);
     }
-    for (; xq < x1; ++xq) {
-        double y[NB];
-#pragma unroll
-        for (int k = 0; k < NB; ++k) y[k] = inv_dist<MASK>(bx[k], d2[k], xs[xq], drop2);
-        const double* wf = row + (long long)xq * R;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int k = 0; k < NB; ++k) acc[k][r] = fma(wf[r], y[k], acc[k][r]);
-    }
+    parities(k);
+}
+
+__device__ __forceinline__ void yz_dist(double by, double bz, double ay, double az, double (&d)[4]) {
+    const double ym = by - ay, yp = by + ay, zm = bz - az, zp = bz + az;
+    const double zm2 = zm * zm, zp2 = zp * zp;
+    d[0] = fma(ym, ym, zm2);
+    d[1] = fma(yp, yp, zm2);
+    d[2] = fma(ym, ym, zp2);
+    d[3] = fma(yp, yp, zp2);
 }
 
 // Work-groups are dispatched to the eight XCDs round robin (w % 8).  Give XCD x a contiguous
 // range of the logical work-group order, in which consecutive work-groups are the boundary
-// tiles of one part of the lattice: the tiles in flight on an XCD then stream the same
+// tiles of one part of the octant: the tiles in flight on an XCD then stream the same
 // records through its L2.
 __device__ __forceinline__ int quad_xcd_remap(int w, int G) {
     constexpr int NXCD = 8;
@@ -141,97 +236,220 @@ __device__ __forceinline__ int quad_xcd_remap(int w, int G) {
     return x * base + min(x, rem) + slot;
 }
 
-// boundary node -> lattice indices (face order x-, x+ [Z][Y]; y-, y+ [Z][X]; z-, z+ [Y][X])
-__device__ __forceinline__ void face_node(int bb, int NX, int NY, int NZ, int& X, int& Y, int& Z) {
-    const int fx = NZ * NY, fy = NZ * NX, fz = NY * NX;
-    if (bb < 2 * fx) {
-        const int side = bb >= fx, rem = bb - side * fx;
-        Z = rem / NY; Y = rem % NY; X = side ? NX - 1 : 0;
-    } else if (bb < 2 * fx + 2 * fy) {
-        const int t = bb - 2 * fx, side = t >= fy, rem = t - side * fy;
-        Z = rem / NX; X = rem % NX; Y = side ? NY - 1 : 0;
-    } else {
-        const int t = bb - 2 * fx - 2 * fy, side = t >= fz, rem = t - side * fz;
-        Y = rem / NX; X = rem % NX; Z = side ? NZ - 1 : 0;
-    }
+// distances from the centre of the box of lattice node X and its axis table
+__device__ __forceinline__ double centred(const double* __restrict__ x, int N, int X) {
+    return 0.5 * (x[0] + x[N - 1]) - x[X];
+}
+
+// Parity sums of the octant boundary node: slot of image s in the part's face vector.  A parity that is
+// odd on an axis where the node is its own image has a zero sum and no slot of its own.
+__device__ __forceinline__ void store_parity(double* __restrict__ o, int b, int s, const QuadDims& D, double v) {
+    int f, X, Y, Z;
+    oct_face_node(b, D, f, X, Y, Z);
+    if (!(s & self_mask(X, Y, Z, D))) o[face_slot(f, X, Y, Z, s, D)] = v;
 }
 
 template <int R>
 __global__ __launch_bounds__(QUAD_BLOCK) void k_quad(const double* __restrict__ xs, const double* __restrict__ ys,
-                                              const double* __restrict__ zs, int NX, int NY, int NZ, int nface,
-                                              int zper, int ntb, double drop2, const double* __restrict__ rec,
-                                              double* __restrict__ out, int nsrc, int r0, int direct) {
-    constexpr int NB = QUAD_NB;
-    // logical work-group: boundary tile (fastest) and part of the lattice
+                                                     const double* __restrict__ zs, QuadDims D, int nface, int nper,
+                                                     int ntb, double drop2, const double* __restrict__ rec,
+                                                     double* __restrict__ out) {
+    // logical work-group: boundary tile (fastest) and part of the octant
     const int w = quad_xcd_remap(blockIdx.x, gridDim.x);
     const int tile = w % ntb, part = w / ntb;
-    int bnode[NB];
-    double bx[NB], by[NB], bz[NB];
+    const int b = tile * QUAD_BLOCK + threadIdx.x;
+    int f, X, Y, Z;
+    oct_face_node(min(b, D.nbo - 1), D, f, X, Y, Z);
+    const double bx = centred(xs, D.N[0], X), by = centred(ys, D.N[1], Y), bz = centred(zs, D.N[2], Z);
+    double acc[8][R];
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        bnode[k] = tile * (QUAD_BLOCK * NB) + k * QUAD_BLOCK + threadIdx.x;
-        int X, Y, Z;
-        face_node(bnode[k] < nface ? bnode[k] : nface - 1, NX, NY, NZ, X, Y, Z);
-        bx[k] = xs[X]; by[k] = ys[Y]; bz[k] = zs[Z];
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[s][r] = 0.0;
+    const double cx = 0.5 * (xs[0] + xs[D.N[0] - 1]);
+    int q = part * nper;
+    const int q1 = min(D.noct, q + nper);
+    auto pair = [&](auto mask, const double (&d)[4], double ax, const double* __restrict__ F) {
+        double k[8];
+        pair_kernel<decltype(mask)::value>(bx, ax, d, drop2, k);
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[s][r] = fma(F[s * R + r], k[s], acc[s][r]);
+    };
+    while (q < q1) {
+        // the rest of one lattice row; only rows on the boundary surface, and the first node of any
+        // other row, can meet the boundary node itself
+        const int row = q / D.H[0], x0 = q - row * D.H[0], x1 = min(D.H[0], x0 + q1 - q);
+        const int yq = row % D.H[1], zq = row / D.H[1];
+        double d[4];
+        yz_dist(by, bz, centred(ys, D.N[1], yq), centred(zs, D.N[2], zq), d);
+        const double* F = rec + (long long)row * D.H[0] * (8 * R);
+        const int m1 = yq == 0 || zq == 0 ? x1 : min(x1, max(x0, 1));
+        int x = x0;
+        for (; x < m1; ++x) pair(std::true_type{}, d, cx - xs[x], F + (long long)x * (8 * R));
+#pragma unroll 2
+        for (; x < x1; ++x) pair(std::false_type{}, d, cx - xs[x], F + (long long)x * (8 * R));
+        q += x1 - x0;
     }
-    double acc[NB][R];
+    if (b >= D.nbo) return;
 #pragma unroll
-    for (int k = 0; k < NB; ++k)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int r = 0; r < R; ++r) acc[k][r] = 0.0;
-    const int z0 = part * zper, z1 = min(NZ, z0 + zper);
-    for (int zq = z0; zq < z1; ++zq) {
-        double dz2[NB];
+        for (int s = 0; s < 8; ++s) store_parity(out + ((long long)part * R + r) * nface, b, s, D, acc[s][r]);
+}
+
+// R = 16 NT sources: a wave owns 16 octant boundary nodes, a work-group 64.
+template <int NT>
+__global__ __launch_bounds__(QUAD_BLOCK, 2) void k_quad_mfma(const double* __restrict__ xs,
+                                                             const double* __restrict__ ys,
+                                                             const double* __restrict__ zs, QuadDims D, int nface,
+                                                             int nper, int ntb, double drop2,
+                                                             const double* __restrict__ rec,
+                                                             double* __restrict__ out) {
+    constexpr int R = 16 * NT, NV = 8 * R;               // values of a node's record
+    constexpr int NS = NV + 16;                          // its LDS stride: two nodes fall on different banks
+    constexpr int LD = QUAD_CHUNK * NV / (2 * QUAD_BLOCK);  // double2 a thread stages per chunk
+    static_assert(LD * 2 * QUAD_BLOCK == QUAD_CHUNK * NV, "chunk is not a whole number of loads");
+    __shared__ double sF[2][QUAD_CHUNK * NS];
+    const int w = quad_xcd_remap(blockIdx.x, gridDim.x);
+    const int tile = w % ntb, part = w / ntb;
+    const int t = threadIdx.x, lane = t & 63, m = lane & 15, kq = lane >> 4;
+    const int b0 = tile * 64 + (t >> 6) * 16;
+    int f, X, Y, Z;
+    oct_face_node(min(b0 + m, D.nbo - 1), D, f, X, Y, Z);
+    const double bx = centred(xs, D.N[0], X), by = centred(ys, D.N[1], Y), bz = centred(zs, D.N[2], Z);
+    const double cx = 0.5 * (xs[0] + xs[D.N[0] - 1]), cy = 0.5 * (ys[0] + ys[D.N[1] - 1]),
+                 cz = 0.5 * (zs[0] + zs[D.N[2] - 1]);
+    v4d acc[8][NT];
 #pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            const double dz = bz[k] - zs[zq];
-            dz2[k] = dz * dz;
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[s][n] = v4d{0.0, 0.0, 0.0, 0.0};
+    const int q0 = part * nper, q1 = min(D.noct, q0 + nper);
+    const long long vend = (long long)q1 * NV;  // records end here; a last chunk is filled up with zeros
+    double2 st[LD];
+    auto stage_load = [&](int q) {
+#pragma unroll
+        for (int i = 0; i < LD; ++i) {
+            const long long v = (long long)q * NV + 2 * (i * QUAD_BLOCK + t);
+            st[i] = v < vend ? *reinterpret_cast<const double2*>(rec + v) : double2{0.0, 0.0};
         }
-        const bool zedge = zq == 0 || zq == NZ - 1;
-        for (int yq = 0; yq < NY; ++yq) {
-            double d2[NB];
+    };
+    auto stage_store = [&](int buf) {
 #pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const double dy = by[k] - ys[yq];
-                d2[k] = fma(dy, dy, dz2[k]);
+        for (int i = 0; i < LD; ++i) {
+            const int v = 2 * (i * QUAD_BLOCK + t);
+            *reinterpret_cast<double2*>(&sF[buf][(v / NV) * NS + v % NV]) = st[i];
+        }
+    };
+    // the lane's grid node (x fastest), advanced by four nodes per MFMA step; past the end it stays on the
+    // last plane, where its record is zero
+    const int HX = D.H[0], HY = D.H[1], HZ = D.H[2];
+    int xq, yq, zq;
+    {
+        const int q = q0 + kq;
+        xq = q % HX;
+        yq = (q / HX) % HY;
+        zq = q / (HX * HY);
+    }
+    stage_load(q0);
+    stage_store(0);
+    int buf = 0;
+    for (int q = q0; q < q1; q += QUAD_CHUNK, buf ^= 1) {
+        __syncthreads();  // this chunk is staged; the other buffer's readers are done
+        const bool more = q + QUAD_CHUNK < q1;
+        if (more) stage_load(q + QUAD_CHUNK);
+#pragma unroll
+        for (int step = 0; step < QUAD_CHUNK / 4; ++step) {
+            double d[4], k[8];
+            const int zc = min(zq, HZ - 1);
+            yz_dist(by, bz, cy - ys[yq], cz - zs[zc], d);
+            const double ax = cx - xs[xq];
+            if (__any(xq == 0 || yq == 0 || zc == 0))
+                pair_kernel<true>(bx, ax, d, drop2, k);
+            else
+                pair_kernel<false>(bx, ax, d, drop2, k);
+            const double* F = &sF[buf][(step * 4 + kq) * NS + m];
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+                    acc[s][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(k[s], F[s * R + n * 16], acc[s][n], 0, 0, 0);
+            xq += 4;
+            while (xq >= HX) {
+                xq -= HX;
+                if (++yq == HY) {
+                    yq = 0;
+                    ++zq;
+                }
             }
-            const double* row = rec + ((long long)zq * NY + yq) * NX * R;
-            // a row on the lattice's boundary surface is tested node by node; any other row
-            // only at its two end nodes (x faces).  Three consecutive ranges, no branches,
-            // so that one set of accumulators serves all of them.
-            const bool edge = zedge || yq == 0 || yq == NY - 1;
-            const int m1 = edge ? NX : 1, u1 = edge ? NX : NX - 1;
-            quad_run<R, NB, true>(bx, d2, xs, row, 0, m1, drop2, acc);
-            quad_run<R, NB, false>(bx, d2, xs, row, m1, u1, drop2, acc);
-            quad_run<R, NB, true>(bx, d2, xs, row, u1, NX, drop2, acc);
         }
+        if (more) stage_store(buf ^ 1);
     }
-    // direct: out is g [nsrc][nface]; else the split's partial sums [split][R][nface]
+    // accumulator: source = lane & 15, boundary node = lane / 16 + 4 * register
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        if (bnode[k] >= nface) continue;
-        double* o = direct ? out + (long long)r0 * nface + bnode[k] : out + (long long)part * R * nface + bnode[k];
+    for (int i = 0; i < 4; ++i) {
+        const int b = b0 + kq + 4 * i;
+        if (b >= D.nbo) continue;
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (r0 + r < nsrc) o[(long long)r * nface] = acc[k][r];
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                store_parity(out + ((long long)part * R + n * 16 + m) * nface, b, s, D, acc[s][n][i]);
     }
 }
 
-__global__ __launch_bounds__(256) void k_quad_sum(const double* __restrict__ part, int S, int R, int nface,
-                                                  int nsrc, int r0, double* __restrict__ g) {
+// g at the eight images of an octant boundary node from its parity sums (S parts, face vectors `stride`
+// sources apart; part and g may be the same vectors).  A source with a value that is not finite has parity
+// sums that are not finite either; its data are then formed from its non-finite terms alone, as the plain
+// sum over all nodes would have them (an infinite value stays one, rather than infinity minus infinity).
+__global__ __launch_bounds__(256) void k_quad_combine(const double* part, int S, int R, QuadDims D, int nface,
+                                                      int nr, int r0, const LevelDev<double>* __restrict__ dev,
+                                                      int n, long long ndof, const double* __restrict__ xs,
+                                                      const double* __restrict__ ys, const double* __restrict__ zs,
+                                                      double drop2, const double* __restrict__ f,
+                                                      const double* __restrict__ phi, const int* __restrict__ pi,
+                                                      const int* __restrict__ pj, double* g) {
     const long long t = blockIdx.x * 256LL + threadIdx.x;
-    const int nr = min(R, nsrc - r0);
-    if (t >= (long long)nr * nface) return;
-    double acc = 0.0;
-    for (int s = 0; s < S; ++s) acc += part[(long long)s * R * nface + t];
-    g[(long long)r0 * nface + t] = acc;
-}
-
-template <int R>
-void launch_quad_r(int ntb, int S, const double* nodes, int NX, int NY, int NZ, int nface, int zper, double drop2,
-                   const double* rec, double* out, int nsrc, int r0, int direct, hipStream_t s) {
-    hipLaunchKernelGGL(k_quad<R>, dim3((unsigned)(ntb * S)), dim3(QUAD_BLOCK), 0, s, nodes, nodes + NX,
-                       nodes + NX + NY, NX, NY, NZ, nface, zper, ntb, drop2, rec, out, nsrc, r0, direct);
+    if (t >= (long long)nr * D.nbo) return;
+    const int r = (int)(t / D.nbo), b = (int)(t % D.nbo);
+    int fc, X, Y, Z;
+    oct_face_node(b, D, fc, X, Y, Z);
+    const int self = self_mask(X, Y, Z, D);
+    double v[8];
+    bool finite = true;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const int slot = face_slot(fc, X, Y, Z, s, D);
+        double a = 0.0;
+        if (!(s & self))
+            for (int p = 0; p < S; ++p) a += part[((long long)p * R + r) * nface + slot];
+        v[s] = a;
+        finite &= isfinite(a);
+    }
+    parities(v);
+    if (!finite) {
+        double bad[8] = {};
+        bool any = false;
+        for (int zq = 0; zq < D.N[2]; ++zq)
+            for (int yq = 0; yq < D.N[1]; ++yq)
+                for (int xq = 0; xq < D.N[0]; ++xq) {
+                    const double a = quad_source(r0 + r, xq, yq, zq, D, n, ndof, dev, f, phi, pi, pj);
+                    if (isfinite(a)) continue;
+                    any = true;
+                    for (int s = 0; s < 8; ++s) {
+                        const double dx = xs[s & 1 ? D.N[0] - 1 - X : X] - xs[xq];
+                        const double dy = ys[s & 2 ? D.N[1] - 1 - Y : Y] - ys[yq];
+                        const double dz = zs[s & 4 ? D.N[2] - 1 - Z : Z] - zs[zq];
+                        bad[s] = fma(a, inv_dist<true>(fma(dx, dx, fma(dy, dy, dz * dz)), drop2), bad[s]);
+                    }
+                }
+        if (any)
+            for (int s = 0; s < 8; ++s) v[s] = 8.0 * bad[s];
+    }
+#pragma unroll
+    for (int s = 0; s < 8; ++s) g[(long long)(r0 + r) * nface + face_slot(fc, X, Y, Z, s, D)] = 0.125 * v[s];
 }
 
 }  // namespace
@@ -267,90 +485,115 @@ double* quad_scratch(int device, long long* capacity) {
     return g_scratch[device];
 }
 
-QuadPlan quad_plan(const LevelHost& L, int nsrc) {
+namespace {
+
+// Most parts the octant is split into for tiles of R sources.  The same for every width of the vector
+// kernel, so that a source's data do not depend on how many share its call there.
+int quad_parts(const QuadDims& D, int R) {
+    const bool vec = R <= QUAD_VEC;
+    const long long waves = (D.nbo + (vec ? QUAD_BLOCK : 64) - 1) / (vec ? QUAD_BLOCK : 64) * (QUAD_BLOCK / 64);
+    const long long want = ((vec ? QUAD_WAVES_VEC : QUAD_WAVES_MFMA) + waves - 1) / waves;
+    return (int)std::max(1LL, std::min<long long>((D.noct + 63) / 64, want));  // at least 64 nodes a part
+}
+
+// One pass over the octant: source tile, nodes per part, parts (at most `most`).
+struct QuadPass {
+    int R, nper, S;
+};
+QuadPass quad_pass(const QuadDims& D, int left, int rmax, long long part_len, long long nface) {
+    QuadPass T{};
+    T.R = quad_tile(left, rmax);
+    const long long most = std::max(1LL, std::min<long long>(quad_parts(D, T.R), part_len / (T.R * nface)));
+    const int nper = (int)((D.noct + most - 1) / most);
+    T.nper = (nper + QUAD_CHUNK - 1) / QUAD_CHUNK * QUAD_CHUNK;
+    T.S = (D.noct + T.nper - 1) / T.nper;
+    return T;
+}
+// One part of a tile that pads no source leaves its sums in g itself; everything else needs part space.
+bool quad_direct(const QuadPass& T, int left) { return T.S == 1 && T.R <= left; }
+
+// The plan with source tiles of at most rmax in `capacity` doubles; rmax = 0 when it does not fit.
+QuadPlan quad_plan_width(const LevelHost& L, int nsrc, int rmax, long long capacity) {
+    const QuadDims D = quad_dims(L);
     QuadPlan P{};
-    const long long NX = (long long)L.E[0] * L.n, NY = (long long)L.E[1] * L.n, NZ = (long long)L.E[2] * L.n;
-    P.nface = 2 * (NZ * NY + NZ * NX + NY * NX);
-    P.ntile = std::max(1, (nsrc + QUAD_RMAX - 1) / QUAD_RMAX);
-    const int per = (nsrc + P.ntile - 1) / P.ntile;
-    P.R = per < 4 ? per : (per + 3) / 4 * 4;  // 1-3 sources (a single density) unpadded
-    const long long wpb = QUAD_BLOCK / 64, blocks = (P.nface + QUAD_BLOCK * QUAD_NB - 1) / (QUAD_BLOCK * QUAD_NB);
-    const long long want = (QUAD_WAVES + wpb * blocks - 1) / (wpb * blocks);
-    const int S0 = (int)std::max(1LL, std::min(NZ, want));
-    P.zper = (int)((NZ + S0 - 1) / S0);
-    P.S = (int)((NZ + P.zper - 1) / P.zper);
-    P.rec_len = L.ndof * P.R;
-    P.part_len = P.S > 1 ? (long long)P.S * P.R * P.nface : 0;
+    P.nface = 2 * ((long long)D.N[2] * D.N[1] + (long long)D.N[2] * D.N[0] + (long long)D.N[1] * D.N[0]);
+    for (int left = nsrc; left > 0; left -= quad_tile(left, rmax)) {
+        const int R = quad_tile(left, rmax);
+        P.rec_len = std::max(P.rec_len, 8LL * D.noct * R);
+        P.part_len = std::max(P.part_len, (long long)quad_parts(D, R) * R * P.nface);
+    }
+    if (P.rec_len > capacity) return P;
+    P.part_len = std::min(P.part_len, capacity - P.rec_len);
+    P.wgs = 1LL << 40;
+    for (int left = nsrc; left > 0; left -= quad_tile(left, rmax)) {
+        const QuadPass T = quad_pass(D, left, rmax, P.part_len, P.nface);
+        if (!quad_direct(T, left) && (long long)T.S * T.R * P.nface > P.part_len) return P;
+        const int per = T.R <= QUAD_VEC ? QUAD_BLOCK : 64;
+        P.wgs = std::min(P.wgs, (long long)T.S * ((D.nbo + per - 1) / per));
+    }
+    P.rmax = rmax;
     return P;
 }
 
+}  // namespace
+
+QuadPlan quad_plan(const LevelHost& L, int nsrc) {
+    return quad_plan_width(L, nsrc, 32, 1LL << 60);
+}
+
 // A plan whose records and partial sums fit in `capacity` doubles: the widest source tile that
-// still leaves room for enough split parts to give the launch about a thousand work-groups (or
-// the most it can), narrower tiles meaning more passes over the grid.  R = 0: the mesh does not
-// fit even with one source per pass and no split.
+// still leaves room for enough parts to give every launch about two work-groups a CU (or the most
+// it can), narrower tiles meaning more passes over the octant.  rmax = 0: the mesh does not fit even
+// with one source per pass and no split.
 QuadPlan quad_plan_bounded(const LevelHost& L, int nsrc, long long capacity) {
-    const QuadPlan full = quad_plan(L, nsrc);
-    if (nsrc <= 0 || full.rec_len + full.part_len <= capacity) return full;
-    static const int tiles[] = {48, 44, 40, 36, 32, 28, 24, 20, 16, 12, 8, 4, 3, 2, 1};
-    const long long NZ = (long long)L.E[2] * L.n;
-    const long long ntb = (full.nface + QUAD_BLOCK * QUAD_NB - 1) / (QUAD_BLOCK * QUAD_NB);
     QuadPlan best{};
-    long long best_wg = -1;
-    for (int R : tiles) {
-        if (R > full.R) continue;
-        const long long rec = L.ndof * R;
-        if (rec > capacity) continue;
-        const long long smax = std::min<long long>(full.S, (capacity - rec) / ((long long)R * full.nface));
-        const int S0 = (int)std::max(1LL, std::min(NZ, smax));
-        QuadPlan P = full;
-        P.R = R;
-        P.ntile = (nsrc + R - 1) / R;
-        P.zper = (int)((NZ + S0 - 1) / S0);
-        P.S = (int)((NZ + P.zper - 1) / P.zper);
-        P.rec_len = rec;
-        P.part_len = P.S > 1 ? (long long)P.S * R * P.nface : 0;
-        if (P.rec_len + P.part_len > capacity) continue;
-        const long long wg = ntb * P.S;
-        if (wg > best_wg) {
-            best = P;
-            best_wg = wg;
+    for (int rmax : {32, 16, 4, 3, 2, 1}) {
+        const QuadPlan P = quad_plan_width(L, nsrc, rmax, capacity);
+        if (!P.rmax) {
+            if (!best.nface) best = P;
+            continue;
         }
-        if (wg >= std::min<long long>(1024, ntb * full.S)) return P;
+        if (!best.rmax || P.wgs > best.wgs) best = P;
+        if (P.wgs >= 512) return P;
     }
-    return best;  // R = 0 when nothing fits
+    return best;
 }
 
 void launch_quad_data(const LevelHost& L, const LevelDev<double>* dev, const double* nodes, const QuadPlan& P,
                       int nsrc, const double* f, const double* phi, const int* pi, const int* pj, double* rec,
                       double* part, double* g, hipStream_t s) {
     if (nsrc <= 0) return;
-    const int NX = L.E[0] * L.n, NY = L.E[1] * L.n, NZ = L.E[2] * L.n;
-    if (P.nface != 2 * ((long long)NZ * NY + (long long)NZ * NX + (long long)NY * NX) || P.nface > (1LL << 30) ||
-        P.R < 1 || P.R > QUAD_RMAX || (P.R > 3 && P.R % 4) || (P.S > 1 && !part) || (long long)P.S * P.zper < NZ)
+    const QuadDims D = quad_dims(L);
+    const long long nfaces = 2 * ((long long)D.N[2] * D.N[1] + (long long)D.N[2] * D.N[0] + (long long)D.N[1] * D.N[0]);
+    if (P.nface != nfaces || nfaces > (1LL << 30) || L.ndof > (1LL << 30) || P.rmax < 1)
         throw std::logic_error("quadrature plan does not fit the mesh");
     const double hmin = std::min({L.h[0], L.h[1], L.h[2]});
     const double drop2 = (1e-6 * hmin) * (1e-6 * hmin);
-    const int nface = (int)P.nface;
-    const int ntb = (nface + QUAD_BLOCK * QUAD_NB - 1) / (QUAD_BLOCK * QUAD_NB);
-    if ((long long)ntb * P.S >= (1LL << 31)) throw std::logic_error("quadrature grid too large");
-    for (int r0 = 0; r0 < nsrc; r0 += P.R) {
-        hipLaunchKernelGGL(k_quad_pack, dim3((unsigned)((L.ndof + 255) / 256)), dim3(256), 0, s, dev, L.E[0], L.E[1],
-                           L.n, L.ndof, NX, NY, nsrc, r0, P.R, f, phi, pi, pj, rec);
-        const int direct = P.S == 1;
-        double* out = direct ? g : part;
-        switch (P.R) {
-#define QUAD_CASE(RR) \
-    case RR: launch_quad_r<RR>(ntb, P.S, nodes, NX, NY, NZ, nface, P.zper, drop2, rec, out, nsrc, r0, direct, s); break;
-            QUAD_CASE(1) QUAD_CASE(2) QUAD_CASE(3) QUAD_CASE(4) QUAD_CASE(8) QUAD_CASE(12) QUAD_CASE(16) QUAD_CASE(20) QUAD_CASE(24)
-            QUAD_CASE(28) QUAD_CASE(32) QUAD_CASE(36) QUAD_CASE(40) QUAD_CASE(44) QUAD_CASE(48)
+    const int nface = (int)nfaces;
+    const double *xs = nodes, *ys = nodes + D.N[0], *zs = nodes + D.N[0] + D.N[1];
+    for (int r0 = 0; r0 < nsrc;) {
+        const int left = nsrc - r0;
+        const QuadPass T = quad_pass(D, left, P.rmax, P.part_len, P.nface);
+        const bool direct = quad_direct(T, left), vec = T.R <= QUAD_VEC;
+        if (8LL * D.noct * T.R > P.rec_len || (!direct && (!part || (long long)T.S * T.R * nface > P.part_len)))
+            throw std::logic_error("quadrature plan does not fit the mesh");
+        const int per = vec ? QUAD_BLOCK : 64, ntb = (D.nbo + per - 1) / per;
+        if ((long long)ntb * T.S >= (1LL << 31)) throw std::logic_error("quadrature grid too large");
+        hipLaunchKernelGGL(k_quad_pack, dim3((unsigned)((D.noct + PACK_NODES - 1) / PACK_NODES)),
+                           dim3(PACK_NODES * PACK_SRC), 0, s, dev, D, L.n, L.ndof, nsrc, r0, T.R, f, phi, pi, pj, rec);
+        double* out = direct ? g + (long long)r0 * nface : part;
+        switch (T.R) {
+#define QUAD_CASE(K, RR) \
+    case RR: hipLaunchKernelGGL(K, dim3((unsigned)(ntb * T.S)), dim3(QUAD_BLOCK), 0, s, xs, ys, zs, D, nface, T.nper, ntb, drop2, rec, out); break;
+            QUAD_CASE(k_quad<1>, 1) QUAD_CASE(k_quad<2>, 2) QUAD_CASE(k_quad<3>, 3) QUAD_CASE(k_quad<4>, 4)
+            QUAD_CASE(k_quad_mfma<1>, 16) QUAD_CASE(k_quad_mfma<2>, 32)
 #undef QUAD_CASE
             default: throw std::logic_error("no quadrature kernel for this tile");
         }
-        if (!direct) {
-            const long long cnt = (long long)std::min(P.R, nsrc - r0) * nface;
-            hipLaunchKernelGGL(k_quad_sum, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, part, P.S, P.R,
-                               nface, nsrc, r0, g);
-        }
+        const int nr = std::min(T.R, left);
+        hipLaunchKernelGGL(k_quad_combine, dim3((unsigned)(((long long)nr * D.nbo + 255) / 256)), dim3(256), 0, s, out,
+                           T.S, T.R, D, nface, nr, r0, dev, L.n, L.ndof, xs, ys, zs, drop2, f, phi, pi, pj, g);
+        r0 += nr;
     }
 }
 

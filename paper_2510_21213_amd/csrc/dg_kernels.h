@@ -282,14 +282,15 @@ void launch_small_gemm(int ni, int nk, int na, const double* A, const double* B,
 
 // Dirichlet data by quadrature (dg_boundary.hip): g[s][b] = sum_q W_q f_s(x_q) / |r_b - x_q| over the
 // finest level's nodes, for nsrc sources f (packed fields) or, with f null, the pair products
-// phi[pi[s]] phi[pj[s]].  Sources go in tiles of R; each tile is packed into rec (rec_len
-// doubles) and its Z planes are split S ways (partial sums in part, part_len doubles).
+// phi[pi[s]] phi[pj[s]].  Sources go in tiles of at most rmax (1..4, 16 or 32); each tile's parity
+// records are packed into rec (rec_len doubles) and its octant of nodes is split into parts
+// (partial sums in part, part_len doubles).
 struct QuadPlan {
-    int R, ntile, S, zper;
-    long long nface, rec_len, part_len;
+    int rmax;
+    long long nface, rec_len, part_len, wgs;  // wgs: the fewest work-groups of a pass
 };
 QuadPlan quad_plan(const LevelHost& L, int nsrc);
-// The same with rec_len + part_len <= capacity doubles (R = 0 if the mesh cannot fit).
+// The same with rec_len + part_len <= capacity doubles (rmax = 0 if the mesh cannot fit).
 QuadPlan quad_plan_bounded(const LevelHost& L, int nsrc, long long capacity);
 // The fixed work space of dg_boundary_data_noalloc (a file-scope device array): look up this
 // device's copy once, with the device current (quad_scratch_init), then fetch it and its size

@@ -61,6 +61,32 @@ def test_boundary_data_matches_oracle(gpu_lib, E, p, nsrc):
         assert np.max(np.abs(g[k] - go[k])) <= RTOL * np.max(np.abs(go[k])), k
 
 
+@pytest.mark.parametrize("E,p,nsrc", [((3, 5, 1), 4, 5), ((3, 2, 5), 2, 33), ((2, 2, 2), 1, 17), ((5, 3, 3), 2, 3),
+                                       ((1, 4, 3), 4, 36), ((4, 4, 4), 3, 16), ((7, 5, 3), 4, 4)])
+def test_boundary_data_by_reflections_matches_oracle(gpu_lib, E, p, nsrc):
+    """Odd node counts (nodes that are their own mirror image on one, two and all three axes), a
+    few nodes per half axis, and every source tile: the vector kernel's widths, a full and a padded
+    matrix tile, a wide tile followed by a vector pass (36) and by a single source (33)."""
+    test_boundary_data_matches_oracle(gpu_lib, E, p, nsrc)
+
+
+@pytest.mark.parametrize("nsrc", [3, 6])
+def test_boundary_data_of_values_that_are_not_finite(gpu_lib, nsrc):
+    """An infinite source value makes its source's data infinite of the same sign (the plain sum's
+    value, not infinity minus infinity between mirror images), a NaN makes them NaN, and the other
+    sources of the call are untouched."""
+    mesh = _mesh((3, 2, 2), 4, [-1.5, -1.0, -1.2], [1.5, 1.0, 1.0])
+    ctx = gpu_lib.Context([(mesh.E, mesh.p, mesh.lo, mesh.hi)])
+    xyz, _ = ctx.mesh_coords(0)
+    f = np.stack([_sources(xyz[0], xyz[1], xyz[2], k) for k in range(nsrc)])
+    ref = ctx.boundary_data(_t(f.reshape(-1))).cpu().numpy().reshape(nsrc, -1)
+    inner = 62   # the centre node of the first element
+    f[0, inner], f[1, inner] = -np.inf, np.nan
+    g = ctx.boundary_data(_t(f.reshape(-1))).cpu().numpy().reshape(nsrc, -1)
+    assert np.all(g[0] == -np.inf) and np.all(np.isnan(g[1]))
+    assert np.array_equal(g[2:], ref[2:])
+
+
 def test_boundary_data_zero_sources_and_errors(gpu_lib):
     import torch
     ctx = gpu_lib.Context([((2, 2, 2), 2, [-1.0] * 3, [1.0] * 3)])
