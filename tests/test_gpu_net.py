@@ -51,6 +51,28 @@ def test_forward_backward_match_oracle(gpu_lib, levels, E):
     assert np.abs(g - g_ref).max() <= 2e-4 * np.abs(g_ref).max()
 
 
+@pytest.mark.parametrize("levels,E,C,cin,cout,B,shift", [(2, (9, 2, 5), 36, 12, 30, 3, 0), (1, (1, 1, 1), 5, 3, 2, 1, 0),
+                                                         (3, (7, 5, 3), 32, 125, 27, 2, 1), (2, (4, 4, 4), 64, 27, 8, 1, 1)])
+def test_backward_at_the_edges_of_its_tiles(gpu_lib, levels, E, C, cin, cout, B, shift):
+    """Channel counts past a 32-channel tile and not a multiple of 4, ragged and single voxels, and an
+    upstream gradient that does not start on 16 bytes: the same bound as the other backward test."""
+    specs = convnet.layer_specs(levels, C, cin, cout)
+    n = convnet.param_count(specs)
+    rng = np.random.default_rng(50 + C)
+    params = (0.3 * rng.standard_normal(n)).astype(np.float32)
+    net = gpu_lib.Net(levels, C, cin, cout)
+    net.set_params(params)
+    net.set_bf16(False)
+    x = rng.standard_normal((B, E[2], E[1], E[0], cin)).astype(np.float32)
+    dy = rng.standard_normal((B, E[2], E[1], E[0], cout)).astype(np.float32)
+    _, cache = convnet.forward(params.astype(np.float64), specs, levels, x.astype(np.float64))
+    net.forward(_t(x, np.float32), E, B)
+    up = _t(np.concatenate([np.zeros(shift, dtype=np.float32), dy.reshape(-1)]), np.float32)[shift:]
+    g = net.backward(up).cpu().numpy()
+    g_ref = convnet.backward(params.astype(np.float64), specs, levels, cache, dy.astype(np.float64))
+    assert np.abs(g - g_ref).max() <= 2e-4 * np.abs(g_ref).max()
+
+
 @pytest.mark.parametrize("levels,E,C,cin", [(3, (6, 4, 5), 8, 27), (4, (8, 8, 8), 32, 125), (2, (5, 3, 4), 16, 64)])
 def test_inference_with_bf16_activations(gpu_lib, levels, E, C, cin):
     """The guess's forward stores every activation in BF16 (half the bytes of FP32).  The
