@@ -560,10 +560,9 @@ dg_status dg_octree_vcycle(dg_octree* octree, int nrhs, const double* r, double*
  * call and when a call needs more). */
 dg_status dg_octree_exchange(dg_octree* octree, int norb, const double* phi, const double* g_pairs, double* v_pairs,
                              double* W, double* K, double* e_x, dg_rhs_stats* stats, void* stream);
-/* Tuning: right-hand sides per work-group of the octree operator kernels (1, 2 or 4; 0, the
- * default: 4 in FP32 and at degree 4 in FP64, 2 below, the fastest measured on MI355X):
- * the right-hand sides of a work-group share its element's geometry, pieces and tables, and
- * give each thread independent work between its barriers.  Results do not depend on it. */
+/* Tuning: right-hand sides a work-group of the octree operator kernels takes at a time (1, 2 or
+ * 4; 0, the default: 2, the fastest measured on MI355X; 4 is taken as 2).  Results do not depend
+ * on it. */
 dg_status dg_octree_set_rhs_per_block(dg_octree* octree, int rhs_per_block);
 /* x = A^-1 b by FP64 MG-PCG from x = 0, stopping at ||r|| <= rtol ||b|| (recurrence residual) or
  * max_iter; stats (host, may be NULL) as for dg_poisson_solve_batch; returns the worst status. */

@@ -9,20 +9,25 @@
 // z, y, x lexicographic, x fastest; children likewise by their half along each split axis);
 // degree-q GL nodes [k][j][i] per element.
 //
-// Operator.  Matrix-free, one work-group slot per element and right-hand side: the volume term
-// as three 1D contractions with the element's own scale factors, then the six faces of the
-// element.  A face is tiled by "pieces", the intersections with the neighbours' faces (dyadic
-// cells: along each tangential axis the piece is the smaller of the two intervals).  On a piece
-// both sides' traces and normal derivatives are interpolated to the piece's (q+1)^2 GL points
-// with 1D tables (interval j of 2^k of the element's face; k = 0 is the identity), the SIPDG
-// flux is formed there, and its test-function side is projected back onto the element's face
-// nodes.  Each element gathers its own rows (no atomics); every interior piece is computed from
+// Operator.  Matrix-free; a work-group holds an element (several at low degree) for a few
+// right-hand sides.  Everything along one axis acts on node lines: the volume term, and on a
+// conforming or boundary face the traces of the line and of the neighbour's line behind it, the
+// flux at the line's face point and its two test-function sides.  So a thread owns one line of one
+// axis, both of its faces included, and the element needs one exchange through LDS (its nodes in,
+// the three axes' results out).  A hanging face is tiled by "pieces", the intersections with the
+// neighbours' faces (dyadic cells: along each tangential axis the piece is the smaller of the two
+// intervals).  On a piece both sides' traces and normal derivatives are interpolated to the piece's
+// (q+1)^2 GL points with 1D tables (interval j of 2^k of the element's face; k = 0 is the identity),
+// the SIPDG flux is formed there, and its test-function side is projected back onto the element's
+// face nodes; a group of lanes of one wave does a whole face, piece after piece, with no work-group
+// barrier.  Each element gathers its own rows (no atomics); every interior piece is computed from
 // both sides.
 //
 // Multigrid.  Degree steps on the leaves, then mesh steps (the tree cut at generation g, g =
 // G-1 .. 0) at degree 1; the coarsest level is the uniform base mesh at degree 1, solved by
 // fast diagonalisation.  Chebyshev-Jacobi smoothing with the uniform mesh's parameters; the
-// Chebyshev step is fused into the operator kernel's epilogue.  The V-cycle runs in FP64, or
+// Chebyshev step is fused into the operator kernel's epilogue (four fields a step: the iterate,
+// the one before, the source and the new one).  The V-cycle runs in FP64, or
 // in FP32 under the FP64 CG (DG_PREC_FP32_PC): the kernels are templated on the field type.
 #include <hip/hip_runtime.h>
 
@@ -40,18 +45,20 @@
 namespace dg {
 namespace oct {
 
-constexpr int OT = 128;     // threads of an operator work-group
 constexpr int KMAX = 8;     // deepest interpolation table entry (a level jump of 2^8 along an axis)
 constexpr int NTAB = (2 << KMAX) - 1;
+constexpr int TLDS = 7;     // table entries a work-group keeps in LDS (level jumps of up to 4)
 
 struct Piece {
     int nb;        // neighbour element, -1 on the domain boundary
     int s1, s2;    // table entries: this element's face nodes -> the piece's points, along t1 and t2
     int n1, n2;    // the same for the neighbour's face
     int face;      // face of this element: 2 d + (upper side), d the normal axis
+    int el, pad;   // this element
     double sig;    // penalty of the piece
     double wsc;    // product of the piece's two tangential half-widths
     double ijn;    // 1 / (the neighbour's half-width along the normal), 0 on the boundary
+    double ij;     // 1 / (this element's)
 };
 
 template <int N, typename T = double>
@@ -60,6 +67,25 @@ struct Ref {
     T w[N];
     T eL[N], eR[N];      // basis values at -1 and +1
     T dL[N], dR[N];      // basis derivatives there (reference coordinate)
+};
+
+// The reference data of the operator kernel in the field type.  The nodes are symmetric about the centre
+// (eL[i] = eR[N-1-i], dL[i] = -dR[N-1-i], K1 invariant under the reflection), so a line is taken as its even
+// and odd parts x_i +- x_(N-1-i), i < H (the middle node of an odd count counts with the even part).
+template <int N, typename T>
+struct OpRef {
+    static constexpr int H = N / 2, HE = (N + 1) / 2;
+    T w[N], eR[N], dR[N];
+    T Ke[HE][HE], Ko[H][H];  // volume: even and odd rows
+    T se[HE], so[H];         // value at the right end = sum se even + sum so odd, at the left its difference
+    T pe[HE], qo[H];         // derivative likewise (at the left: odd - even)
+};
+
+// One face of an element: its only piece's neighbour where that piece is the whole face of both sides
+// (-1: domain boundary), or -2 and its range among the level's hanging pieces.
+struct Face {
+    int nb, first, count, pad;
+    double sig, ijn;   // of the only piece
 };
 
 enum { OP_APPLY = 0, OP_RESID = 1, OP_CHEB = 2 };
@@ -71,374 +97,372 @@ enum { OP_APPLY = 0, OP_RESID = 1, OP_CHEB = 2 };
             hip_fail(std::string(#x) + ": " + hipGetErrorString(e_) + " at line " + std::to_string(__LINE__)); \
     } while (0)
 
-// y = A u (APPLY), y = f - A u (RESID), or one fused Chebyshev step (CHEB, u = the current
-// correction d): z += d; r -= A d; y = c1 d + c2 D^-1 r.  Grid (element blocks, nrhs); a block
-// holds EPB = 128 / N^3 element slots of N^3 threads.  The pieces of an element (all six faces,
-// stored consecutively) are taken N at a time, N^2 threads per piece: traces of both sides, the
-// two interpolation passes to the piece's points, the flux, the two transposed passes back onto
-// the element's face nodes; then every node thread adds what the pass's pieces give its own row.
+// Work-group of the operator kernel: four waves, a thread per line (3 N^2 an element): 225, 240, 243, 252
+// lines at N = 5, 4, 3, 2, for RB right-hand sides at a time.
+constexpr int OT = 256;
+constexpr int op_epb(int N) { return OT / (3 * N * N); }
+constexpr int OP_WGS = 4096;
+
+// out = A u (APPLY), out = f - A u (RESID), or one Chebyshev step (CHEB) from the iterate u:
+// out = u + c1 (u - uprev) + c2 D^-1 (f - A u); out may be uprev's buffer; uprev null: zero.
+// Grid (element blocks, chunks of at most 64 right-hand sides); a work-group keeps its elements' faces and
+// takes the chunk's right-hand sides RB at a time.
+//
+// What bounds it: waiting on memory (a chain of face record, piece, neighbour's line, 2,000 to 4,000 cycles a
+// link) and vector issue, about 40 % each of an FP32 wave's time at N = 5.  So the chain is walked once for a
+// chunk, and the next right-hand sides' nodes, neighbour lines and hanging neighbours' lines are asked for
+// while the present ones are computed.  Four waves a work-group: with five (a thread per line and right-hand
+// side) only one fitted a CU.  Registers: three waves per SIMD in FP32 at N = 5, two in FP64.
+// Measured (2,836 elements, N = 5, 36 right-hand sides; before: a thread per node, the pieces N at a time with
+// up to seven barriers a pass): FP32 product 238 -> 165 us, FP64 346 -> 276 us; level of degree 2 (FP32)
+// 83 -> 41 us; without hanging faces 76 us per as many elements.  The whole FP32-V-cycle solve 266 -> 174 ms.
+// Tried: neighbour elements staged whole in LDS axis by axis (194 us), four right-hand sides a thread without
+// the prefetch (205 us), a hanging face per lane group instead of a piece (207 us).
 template <int N, int MODE, int RB, typename T>
-__global__ __launch_bounds__(OT) void k_oct_op(Ref<N, double> Rarg, int ne, int nrhs, const double* __restrict__ J,
-                                              const int* __restrict__ fstart, const Piece* __restrict__ pcs,
-                                              const T* __restrict__ tab, const RhsState* __restrict__ st,
-                                              const T* __restrict__ u, T* __restrict__ y,
-                                              const T* __restrict__ f, T* __restrict__ r,
-                                              T* __restrict__ z, const T* __restrict__ dinv, T c1, T c2) {
-    constexpr int N2 = N * N, N3 = N * N * N, EPB = OT / N3;
+__global__ __launch_bounds__(OT, sizeof(T) == 4 ? (N == 5 ? 3 : 4) : 2) void k_oct_op(OpRef<N, T> R, int ne, int nrhs, int chunk, const T* __restrict__ geo,
+                                              const Face* __restrict__ faces, const int* __restrict__ hstart,
+                                              const Piece* __restrict__ pcs, const T* __restrict__ tab,
+                                              const RhsState* __restrict__ st, const T* u, const T* uprev, const T* __restrict__ f, T* out,
+                                              const T* __restrict__ dinv, T c1, T c2) {
+    constexpr int N2 = N * N, N3 = N2 * N, EPB = op_epb(N), NW = OT / 64, HN = N / 2, HE = (N + 1) / 2;
+    constexpr int NODES = EPB * N3, IT = (NODES + OT - 1) / OT;  // nodes of a right-hand side, rounds of the threads
+    // hanging pieces: a lane group of N^2 face nodes each, TPW of them a wave, PR times over
+    constexpr int GL = N2, TPW = 64 / GL, PPR = NW * TPW, PR = N == 5 ? 2 : 1, PS = PPR * PR;
     __shared__ T U[RB][EPB][N3];
-    // per right-hand side and slot, per piece of the pass (N pieces of N^2 points): own /
-    // neighbour trace and normal derivative, the interpolation scratch, the flux, and the result
-    // on the face nodes
-    __shared__ T A0[RB][EPB][N3], A1[RB][EPB][N3], A2[RB][EPB][N3], A3[RB][EPB][N3];
-    __shared__ T B0[RB][EPB][N3], B1[RB][EPB][N3], B2[RB][EPB][N3], B3[RB][EPB][N3];
-    __shared__ int npc[EPB], ncc[EPB];
-    __shared__ Ref<N, T> R;  // the reference data, indexed at run time (from LDS, not the argument block)
-    const int rhs0 = blockIdx.y * RB;
-    bool live[RB];
-    bool any = false;
-#pragma unroll
-    for (int q = 0; q < RB; ++q) {
-        live[q] = rhs0 + q < nrhs && (!st || st[rhs0 + q].active);
-        any = any || live[q];
-    }
-    if (!any) return;
-    const int t = threadIdx.x, s = t / N3, l = t - s * N3;
+    __shared__ T Y[3][RB][EPB][N3];            // the three axes' results
+    __shared__ T H[PS][RB][2][N2];             // hanging pieces: value and derivative sides on the face nodes
+    __shared__ T S[NW][2][RB][64];             // a wave's interpolation passes
+    __shared__ T Tb[TLDS * N2];                // the first interpolation tables
+    __shared__ T w1[N];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const int r0 = blockIdx.y * chunk, nr = min(chunk, nrhs - r0);
+    // right-hand sides of the chunk still iterating
+    const unsigned long long act = __ballot(lane < nr && (!st || st[r0 + lane].active));
+    if (!act) return;
     // work-groups are dealt to the 8 XCDs in turn; give each XCD a contiguous run of elements
     // (depth-first order is spatially local), so that neighbour faces are read from its own L2
     const int nbx = gridDim.x, full = nbx / 8 * 8;
     const int bx = (int)blockIdx.x < full ? ((int)blockIdx.x % 8) * (nbx / 8) + (int)blockIdx.x / 8 : (int)blockIdx.x;
-    const int e = bx * EPB + s;
-    {
-        const double* src = reinterpret_cast<const double*>(&Rarg);
-        T* dst = reinterpret_cast<T*>(&R);
-        for (int q = t; q < (int)(sizeof(Ref<N, double>) / sizeof(double)); q += OT) dst[q] = (T)src[q];
-    }
-    const bool node = s < EPB && e < ne;
+    const int e0 = bx * EPB, nf = 6 * min(EPB, ne - e0), nodes = min(EPB, ne - e0) * N3;
     const long long estride = (long long)ne * N3;
-    const int i = l % N, j = (l / N) % N, k = l / N2;
-    const int pj = l / N2, fl = l - pj * N2;  // piece of the pass and its point / face node
-    if (node) {
+    // the block's hanging pieces, contiguous in the level's list
+    const int h0 = hstart[e0], nh = hstart[min(e0 + EPB, ne)] - h0;
+    // Every load below is made, from a clamped address where its value is not used, so that none waits behind
+    // a branch: the thread's line (element slot, axis, face point (a, b)), ...
+    const int line = t % (3 * N2), ls = min(t / (3 * N2), EPB - 1), d = line / N2, fl = line % N2;
+    const int sd = d == 0 ? 1 : (d == 1 ? N : N2), lo = fl % N * (d == 0 ? N : 1) + fl / N * (d == 2 ? N : N2);
+    const bool haveline = t < 3 * N2 * EPB && e0 + ls < ne;
+    const int el = min(e0 + ls, ne - 1);
+    const Face fL = faces[6 * el + 2 * d], fR = faces[6 * el + 2 * d + 1];
+    const int nbL = fL.nb, nbR = fR.nb;
+    const T sigL = (T)fL.sig, sigR = (T)fR.sig, ijL = (T)fL.ijn, ijR = (T)fR.ijn;
+    const T iJ = geo[6 * el + d], Jt = geo[6 * el + 3 + d];
+    const int hL = nbL == -2 ? fL.first - h0 : 0, hR = nbR == -2 ? fR.first - h0 : 0;  // hanging pieces:
+    const int cL = nbL == -2 ? fL.count : 0, cR = nbR == -2 ? fR.count : 0;            // first and number
+    for (int k = t; k < TLDS * N2; k += OT) Tb[k] = tab[k];
+    if (t == 0) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) w1[k] = R.w[k];
+    }
+    auto base = [&](int rq, int q) { return (long long)(r0 + min(rq + q, nr - 1)) * estride; };
+    auto alive = [&](int rq, int q) { return (act >> (rq + q)) & 1; };
+    // ... the block's nodes, the neighbours' lines (the element's own at a boundary or hanging face)
+    T un[RB][IT], nl[RB][N], nr_[RB][N];
+    auto fetch_nodes = [&](int rq) {
 #pragma unroll
         for (int q = 0; q < RB; ++q)
-            U[q][s][l] = live[q] ? u[(long long)(rhs0 + q) * estride + (long long)e * N3 + l] : T(0);
-    }
-    int p0 = 0, nconf = 0, np = 0;
-    if (node) {
-        p0 = fstart[2 * e];
-        nconf = fstart[2 * e + 1] - p0;
-        np = fstart[2 * e + 2] - p0;
-    }
-    if (node && l == 0) {
-        npc[s] = np - nconf;
-        ncc[s] = nconf;
-    }
-    if (!node && l == 0 && s < EPB) npc[s] = ncc[s] = 0;
-    __syncthreads();
-    T acc[RB];
-    T Jx = T(1), Jy = T(1), Jz = T(1);
 #pragma unroll
-    for (int q = 0; q < RB; ++q) acc[q] = T(0);
-    if (node) {
-        Jx = (T)J[3 * e];
-        Jy = (T)J[3 * e + 1];
-        Jz = (T)J[3 * e + 2];
-        const T sx = Jy * Jz / Jx * R.w[j] * R.w[k], sy = Jx * Jz / Jy * R.w[i] * R.w[k],
-                     sz = Jx * Jy / Jz * R.w[i] * R.w[j];
+            for (int it = 0; it < IT; ++it)
+                un[q][it] = u[base(rq, q) + (long long)e0 * N3 + min(t + it * OT, nodes - 1)];
+    };
+    const long long lineL = (long long)(nbL >= 0 ? nbL : el) * N3 + lo, lineR = (long long)(nbR >= 0 ? nbR : el) * N3 + lo;
+    auto fetch_lines = [&](int rq) {
 #pragma unroll
         for (int q = 0; q < RB; ++q) {
-            T ax = T(0), ay = T(0), az = T(0);
+            const T *ul = u + base(rq, q) + lineL, *ur = u + base(rq, q) + lineR;
 #pragma unroll
-            for (int a = 0; a < N; ++a) {
-                ax += R.K1[i][a] * U[q][s][(k * N + j) * N + a];
-                ay += R.K1[j][a] * U[q][s][(k * N + a) * N + i];
-                az += R.K1[k][a] * U[q][s][(a * N + j) * N + i];
-            }
-            acc[q] = sx * ax + sy * ay + sz * az;
-        }
-    }
-    int npmax = 0, ncmax = 0;
-#pragma unroll
-    for (int q = 0; q < EPB; ++q) {
-        npmax = max(npmax, npc[q]);
-        ncmax = max(ncmax, ncc[q]);
-    }
-    const int o = pj * N2;  // this piece's block of N^2 in the slot arrays
-    // every node adds the pass's pieces (results in A2 / A3): v_s(m) FT[b][a] + sg d_s(m) / J_d FD[b][a]
-#define OCT_GATHER(first, count)                                                                          \
-    for (int q = 0; q < N && q < (count); ++q) {                                                          \
-        const int fq = pcs[(first) + q].face;                                                             \
-        const int dq = fq >> 1;                                                                           \
-        const int m = dq == 0 ? i : (dq == 1 ? j : k);                                                    \
-        const int a = dq == 0 ? j : i;                                                                    \
-        const int b = dq == 2 ? j : k;                                                                    \
-        const T vm = (fq & 1) ? R.eR[m] : R.eL[m];                                                   \
-        const T dm = ((fq & 1) ? R.dR[m] : -R.dL[m]) / (dq == 0 ? Jx : (dq == 1 ? Jy : Jz));         \
-        _Pragma("unroll") for (int c = 0; c < RB; ++c) acc[c] +=                                          \
-            vm * A2[c][s][q * N2 + b * N + a] + dm * A3[c][s][q * N2 + b * N + a];                        \
-    }
-    // conforming pieces and boundary faces (every table entry the identity): the flux at the face
-    // nodes directly, N pieces per pass
-    for (int pass = 0; pass < ncmax; pass += N) {
-        const int pi = pass + pj;
-        if (node && pi < nconf) {
-            const Piece P = pcs[p0 + pi];
-            const bool inner = P.nb >= 0;
-            const int fc = P.face, d = fc >> 1;
-            const int sd = d == 0 ? 1 : (d == 1 ? N : N2);
-            const int s1 = d == 0 ? N : 1;
-            const int s2 = d == 2 ? N : N2;
-            const int a = fl % N, b = fl / N;
-            const T* vS = (fc & 1) ? R.eR : R.eL;
-            const T* dS = (fc & 1) ? R.dR : R.dL;
-            const T* vO = (fc & 1) ? R.eL : R.eR;
-            const T* dO = (fc & 1) ? R.dL : R.dR;
-            const T iJ = T(1) / (d == 0 ? Jx : (d == 1 ? Jy : Jz));
-            const T iJn = (T)P.ijn;
-            const T sg = (fc & 1) ? T(1) : -T(1);
-            const T half = inner ? T(0.5) : T(1);
-            const T W = R.w[a] * R.w[b] * (T)P.wsc;
-            const int lo = a * s1 + b * s2;
-#pragma unroll
-            for (int c = 0; c < RB; ++c) {
-                T tv = T(0), dv = T(0), tn = T(0), dn = T(0);
-#pragma unroll
-                for (int m = 0; m < N; ++m) {
-                    const T x = U[c][s][m * sd + lo];
-                    tv += vS[m] * x;
-                    dv += dS[m] * x;
-                }
-                if (inner && live[c]) {
-                    const T* un = u + (long long)(rhs0 + c) * estride + (long long)P.nb * N3;
-#pragma unroll
-                    for (int m = 0; m < N; ++m) {
-                        const T x = un[m * sd + lo];
-                        tn += vO[m] * x;
-                        dn += dO[m] * x;
-                    }
-                }
-                dv *= iJ;
-                dn *= iJn;
-                const T jmp = inner ? tv - tn : tv;
-                const T davg = inner ? T(0.5) * (dv + dn) : dv;
-                A2[c][s][o + fl] = W * ((T)P.sig * jmp - sg * davg);
-                A3[c][s][o + fl] = W * (-half * jmp);
+            for (int m = 0; m < N; ++m) {
+                nl[q][m] = ul[m * sd];
+                nr_[q][m] = ur[m * sd];
             }
         }
-        __syncthreads();
-        if (node) { OCT_GATHER(p0 + pass, nconf - pass) }
-        __syncthreads();
-    }
-    // hanging pieces: interpolation to the piece's points and back
-    p0 += nconf;
-    np -= nconf;
-    for (int pass = 0; pass < npmax; pass += N) {
-        const int pi = pass + pj;
-        const bool act = node && pi < np;
-        Piece P;
-        P.nb = -1;
-        P.s1 = P.s2 = P.n1 = P.n2 = P.face = 0;
-        P.sig = P.wsc = P.ijn = 0.0;
-        if (act) P = pcs[p0 + pi];
-        const bool inner = P.nb >= 0;
-        const int fc = P.face, d = fc >> 1;
-        // traces on the face nodes (a, b) = (fl % N, fl / N): own face, and the neighbour's opposite face
-        if (act) {
-            const int sd = d == 0 ? 1 : (d == 1 ? N : N2);
-            const int s1 = d == 0 ? N : 1;
-            const int s2 = d == 2 ? N : N2;
-            const int a = fl % N, b = fl / N;
-            const int lo = a * s1 + b * s2;
-            const T* vS = (fc & 1) ? R.eR : R.eL;
-            const T* dS = (fc & 1) ? R.dR : R.dL;
-            const T* vO = (fc & 1) ? R.eL : R.eR;
-            const T* dO = (fc & 1) ? R.dL : R.dR;
-            const T iJ = T(1) / (d == 0 ? Jx : (d == 1 ? Jy : Jz));
-            const T iJn = (T)P.ijn;
+    };
+    // the lane group's hanging pieces hk0, hk0 + PPR, ... of a set of PS, and the neighbours' lines behind them
+    const int sub = lane / GL, gf = lane % N2, ga = gf % N, gb = gf / N;
+    const int hk0 = wave * TPW + min(sub, TPW - 1);
+    const bool grp = lane < TPW * GL;
+    const int la[3] = {ga * N + gb * N2, ga + gb * N2, ga + gb * N};  // the face node's line per normal axis
+    auto line_of = [&](int hd) { return hd == 0 ? la[0] : hd == 1 ? la[1] : la[2]; };
+    auto step_of = [&](int hd) { return hd == 0 ? 1 : hd == 1 ? N : N2; };
+    T hn[PR][RB][N];
+    auto fetch_pieces = [&](int rq, int set) {
 #pragma unroll
-            for (int c = 0; c < RB; ++c) {
-                T tv = T(0), dv = T(0), tn = T(0), dn = T(0);
+        for (int k = 0; k < PR; ++k) {
+            const Piece& P = pcs[h0 + min(set + hk0 + k * PPR, nh - 1)];
+            const int hd = P.face >> 1, hsd = step_of(hd);
 #pragma unroll
-                for (int m = 0; m < N; ++m) {
-                    const T x = U[c][s][m * sd + lo];
-                    tv += vS[m] * x;
-                    dv += dS[m] * x;
-                }
-                if (inner && live[c]) {
-                    const T* un = u + (long long)(rhs0 + c) * estride + (long long)P.nb * N3;
+            for (int q = 0; q < RB; ++q) {
+                const T* v = u + base(rq, q) + (long long)P.nb * N3 + line_of(hd);
 #pragma unroll
-                    for (int m = 0; m < N; ++m) {
-                        const T x = un[m * sd + lo];
-                        tn += vO[m] * x;
-                        dn += dO[m] * x;
-                    }
-                }
-                A0[c][s][o + fl] = tv;
-                A1[c][s][o + fl] = dv * iJ;
-                A2[c][s][o + fl] = tn;
-                A3[c][s][o + fl] = dn * iJn;
+                for (int m = 0; m < N; ++m) hn[k][q][m] = v[m * hsd];
             }
         }
-        __syncthreads();
-        // interpolation along t1: X[b][q1] = sum_a I1[q1][a] F[b][a]
-        if (act) {
-            const int q1 = fl % N, b = fl / N;
-            T Is[N], In[N];
+    };
+    const T half = T(0.5);
+    auto sync = [] {
+        // the lanes of a wave exchange through LDS: its LDS operations are performed in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // x0, x1 through a table along t1 (first) or t2: interpolation, or its transpose
+    auto pass = [&](int entry, bool first, bool back, T (&x0)[RB], T (&x1)[RB]) {
+        T I[N];
+        const int r = first ? ga : gb, at0 = entry * N2 + (back ? r : r * N), at1 = back ? N : 1;
+        if (entry < TLDS) {
 #pragma unroll
-            for (int a = 0; a < N; ++a) {
-                Is[a] = tab[(long long)P.s1 * N2 + q1 * N + a];
-                In[a] = tab[(long long)P.n1 * N2 + q1 * N + a];
-            }
-#pragma unroll
-            for (int c = 0; c < RB; ++c) {
-                T x0 = T(0), x1 = T(0), x2 = T(0), x3 = T(0);
-#pragma unroll
-                for (int a = 0; a < N; ++a) {
-                    x0 += Is[a] * A0[c][s][o + b * N + a];
-                    x1 += Is[a] * A1[c][s][o + b * N + a];
-                    x2 += In[a] * A2[c][s][o + b * N + a];
-                    x3 += In[a] * A3[c][s][o + b * N + a];
-                }
-                B0[c][s][o + fl] = x0;
-                B1[c][s][o + fl] = x1;
-                B2[c][s][o + fl] = x2;
-                B3[c][s][o + fl] = x3;
-            }
-        }
-        __syncthreads();
-        // along t2, and the flux at the piece point (q2, q1); seen from this element (outward
-        // normal sg e_d): [u] = u - u_nb, {d_n u} = sg {du/dx_d}
-        if (act) {
-            const int q1 = fl % N, q2 = fl / N;
-            T Is[N], In[N];
-#pragma unroll
-            for (int b = 0; b < N; ++b) {
-                Is[b] = tab[(long long)P.s2 * N2 + q2 * N + b];
-                In[b] = tab[(long long)P.n2 * N2 + q2 * N + b];
-            }
-            const T sg = (fc & 1) ? T(1) : -T(1);
-            const T half = inner ? T(0.5) : T(1);
-            const T W = R.w[q1] * R.w[q2] * (T)P.wsc;
-#pragma unroll
-            for (int c = 0; c < RB; ++c) {
-                T tr = T(0), dr = T(0), trn = T(0), drn = T(0);
-#pragma unroll
-                for (int b = 0; b < N; ++b) {
-                    tr += Is[b] * B0[c][s][o + b * N + q1];
-                    dr += Is[b] * B1[c][s][o + b * N + q1];
-                    trn += In[b] * B2[c][s][o + b * N + q1];
-                    drn += In[b] * B3[c][s][o + b * N + q1];
-                }
-                const T jmp = inner ? tr - trn : tr;
-                const T davg = inner ? T(0.5) * (dr + drn) : dr;
-                A0[c][s][o + fl] = W * ((T)P.sig * jmp - sg * davg);
-                A1[c][s][o + fl] = W * (-half * jmp);
-            }
-        }
-        __syncthreads();
-        // back onto the face nodes: transpose along t2 ...
-        if (act) {
-            const int q1 = fl % N, b = fl / N;
-            T I2[N];
-#pragma unroll
-            for (int q2 = 0; q2 < N; ++q2) I2[q2] = tab[(long long)P.s2 * N2 + q2 * N + b];
-#pragma unroll
-            for (int c = 0; c < RB; ++c) {
-                T y0 = T(0), y1 = T(0);
-#pragma unroll
-                for (int q2 = 0; q2 < N; ++q2) {
-                    y0 += I2[q2] * A0[c][s][o + q2 * N + q1];
-                    y1 += I2[q2] * A1[c][s][o + q2 * N + q1];
-                }
-                B0[c][s][o + fl] = y0;
-                B1[c][s][o + fl] = y1;
-            }
-        }
-        __syncthreads();
-        // ... and along t1
-        if (act) {
-            const int a = fl % N, b = fl / N;
-            T I1[N];
-#pragma unroll
-            for (int q1 = 0; q1 < N; ++q1) I1[q1] = tab[(long long)P.s1 * N2 + q1 * N + a];
-#pragma unroll
-            for (int c = 0; c < RB; ++c) {
-                T y0 = T(0), y1 = T(0);
-#pragma unroll
-                for (int q1 = 0; q1 < N; ++q1) {
-                    y0 += I1[q1] * B0[c][s][o + b * N + q1];
-                    y1 += I1[q1] * B1[c][s][o + b * N + q1];
-                }
-                A2[c][s][o + fl] = y0;
-                A3[c][s][o + fl] = y1;
-            }
-        }
-        __syncthreads();
-        if (node) { OCT_GATHER(p0 + pass, np - pass) }
-        __syncthreads();
-    }
-    if (!node) return;
-#pragma unroll
-    for (int c = 0; c < RB; ++c) {
-        if (!live[c]) continue;
-        const long long g = (long long)(rhs0 + c) * estride + (long long)e * N3 + l;
-        if constexpr (MODE == OP_APPLY) {
-            y[g] = acc[c];
-        } else if constexpr (MODE == OP_RESID) {
-            y[g] = f[g] - acc[c];
+            for (int m = 0; m < N; ++m) I[m] = Tb[at0 + m * at1];
         } else {
-            const T dv = U[c][s][l];
-            z[g] += dv;
-            const T rn = r[g] - acc[c];
-            r[g] = rn;
-            y[g] = c1 * dv + c2 * dinv[(long long)e * N3 + l] * rn;
+#pragma unroll
+            for (int m = 0; m < N; ++m) I[m] = tab[at0 + m * at1];
         }
+        sync();
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            S[wave][0][q][lane] = x0[q];
+            S[wave][1][q][lane] = x1[q];
+        }
+        sync();
+        const int l0 = lane - gf + (first ? gb * N : ga), l1 = first ? 1 : N;
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            x0[q] = x1[q] = T(0);
+#pragma unroll
+            for (int m = 0; m < N; ++m) {
+                x0[q] += I[m] * S[wave][0][q][l0 + m * l1];
+                x1[q] += I[m] * S[wave][1][q][l0 + m * l1];
+            }
+        }
+    };
+    auto next_live = [&](int rq) {  // the next group with a live right-hand side, or nr
+        while (rq < nr && !((act >> rq) & ((1ull << RB) - 1))) rq += RB;
+        return rq;
+    };
+    int rq = next_live(0);
+    fetch_nodes(rq);
+    if (nh) fetch_pieces(rq, 0);
+    fetch_lines(rq);
+    while (rq < nr) {
+        const int rn = next_live(rq + RB);  // uniform
+#pragma unroll
+        for (int q = 0; q < RB; ++q)
+#pragma unroll
+            for (int it = 0; it < IT; ++it)
+                if (t + it * OT < NODES) (&U[q][0][0])[t + it * OT] = un[q][it];
+        __syncthreads();
+        if (rn < nr) fetch_nodes(rn);
+        T hvL[RB], hwL[RB], hvR[RB], hwR[RB];  // the line's hanging faces
+#pragma unroll
+        for (int q = 0; q < RB; ++q) hvL[q] = hwL[q] = hvR[q] = hwR[q] = T(0);
+        for (int set = 0; set < nh; set += PS) {
+            if (set) {
+                fetch_pieces(rq, set);
+                __syncthreads();  // the last set's results are read
+            }
+#pragma unroll
+            for (int k = 0; k < PR; ++k) {
+                const int hk = set + hk0 + k * PPR;
+                if (!grp || hk >= nh) continue;
+                const Piece& P = pcs[h0 + hk];
+                const int fc = P.face, s = P.el - e0, hd = fc >> 1;
+                const int hsd = step_of(hd), hlo = line_of(hd);
+                const bool up = fc & 1;
+                const int s1 = P.s1, s2 = P.s2, n1 = P.n1, n2 = P.n2;
+                const T W = w1[ga] * w1[gb] * (T)P.wsc, sg = up ? T(1) : -T(1);
+                // traces of both sides on their face nodes
+                T v0[RB], v1[RB], v2[RB], v3[RB];
+#pragma unroll
+                for (int q = 0; q < RB; ++q) v0[q] = v1[q] = v2[q] = v3[q] = T(0);
+#pragma unroll
+                for (int m = 0; m < N; ++m) {
+                    const T eS = up ? R.eR[m] : R.eR[N - 1 - m], eO = up ? R.eR[N - 1 - m] : R.eR[m];
+                    const T dS = up ? R.dR[m] : -R.dR[N - 1 - m], dO = up ? -R.dR[N - 1 - m] : R.dR[m];
+#pragma unroll
+                    for (int q = 0; q < RB; ++q) {
+                        const T x = U[q][s][m * hsd + hlo];
+                        v0[q] += eS * x;
+                        v1[q] += dS * x;
+                        v2[q] += eO * hn[k][q][m];
+                        v3[q] += dO * hn[k][q][m];
+                    }
+                }
+                const T ij = (T)P.ij, ijn = (T)P.ijn, psig = (T)P.sig;
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    v1[q] *= ij;
+                    v3[q] *= ijn;
+                }
+                // interpolation to the piece's points; one side of a piece is usually its whole face (identity
+                // entries)
+                if (s1) pass(s1, true, false, v0, v1);
+                if (n1) pass(n1, true, false, v2, v3);
+                if (s2) pass(s2, false, false, v0, v1);
+                if (n2) pass(n2, false, false, v2, v3);
+                // the flux at the piece point (gb, ga), seen from this element (outward normal sg e_d):
+                // [u] = u - u_nb, {d_n u} = sg {du/dx_d}
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    const T jmp = v0[q] - v2[q];
+                    v0[q] = W * (psig * jmp - sg * (half * (v1[q] + v3[q])));
+                    v1[q] = W * (-half * jmp);
+                }
+                // and back onto the face nodes
+                if (s2) pass(s2, false, true, v0, v1);
+                if (s1) pass(s1, true, true, v0, v1);
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    H[hk - set][q][0][gf] = v0[q];
+                    H[hk - set][q][1][gf] = v1[q];
+                }
+            }
+            __syncthreads();
+            for (int h = max(hL, set); h < min(hL + cL, set + PS); ++h)
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    hvL[q] += H[h - set][q][0][fl];
+                    hwL[q] += H[h - set][q][1][fl];
+                }
+            for (int h = max(hR, set); h < min(hR + cR, set + PS); ++h)
+#pragma unroll
+                for (int q = 0; q < RB; ++q) {
+                    hvR[q] += H[h - set][q][0][fl];
+                    hwR[q] += H[h - set][q][1][fl];
+                }
+        }
+        // what the epilogue will need
+        T fv[RB][IT], pv[RB][IT];
+#pragma unroll
+        for (int q = 0; q < RB; ++q)
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const long long g = base(rq, q) + (long long)e0 * N3 + min(t + it * OT, nodes - 1);
+                fv[q][it] = MODE != OP_APPLY ? f[g] : T(0);
+                pv[q][it] = MODE == OP_CHEB && uprev ? uprev[g] : T(0);
+            }
+        if (nh && rn < nr) fetch_pieces(rn, 0);
+        if (haveline) {
+            const T W = w1[fl % N] * w1[fl / N] * Jt, WJ = W * iJ;
+#pragma unroll
+            for (int q = 0; q < RB; ++q) {
+                T ev[HE], od[HN > 0 ? HN : 1];
+#pragma unroll
+                for (int m = 0; m < HN; ++m) {
+                    const T x0 = U[q][ls][m * sd + lo], x1 = U[q][ls][(N - 1 - m) * sd + lo];
+                    ev[m] = x0 + x1;
+                    od[m] = x0 - x1;
+                }
+                if constexpr (N % 2) ev[HN] = U[q][ls][HN * sd + lo];
+                T S0 = T(0), D0 = T(0), P0 = T(0), Q0 = T(0);
+#pragma unroll
+                for (int m = 0; m < HE; ++m) {
+                    S0 += R.se[m] * ev[m];
+                    P0 += R.pe[m] * ev[m];
+                }
+#pragma unroll
+                for (int m = 0; m < HN; ++m) {
+                    D0 += R.so[m] * od[m];
+                    Q0 += R.qo[m] * od[m];
+                }
+                T tl = T(0), dl = T(0), tr = T(0), dr = T(0);  // the neighbours' facing traces
+#pragma unroll
+                for (int m = 0; m < N; ++m) {
+                    tl += R.eR[m] * nl[q][m];
+                    dl += R.dR[m] * nl[q][m];
+                    tr += R.eR[N - 1 - m] * nr_[q][m];
+                    dr -= R.dR[N - 1 - m] * nr_[q][m];
+                }
+                // the two faces' test-function sides; the derivative side over 1 / J
+                auto flux = [&](bool up, int nb, T sig, T ijn, T tv, T dv, T tn, T dn, T hv, T hw, T& fval, T& fder) {
+                    const T dvj = dv * iJ, dnj = dn * ijn;
+                    const bool inner = nb >= 0;
+                    const T jmp = inner ? tv - tn : tv, davg = inner ? half * (dvj + dnj) : dvj;
+                    fval = W * (sig * jmp + (up ? -davg : davg));
+                    fder = W * (inner ? -half * jmp : -jmp);
+                    if (nb == -2) {
+                        fval = hv;
+                        fder = hw;
+                    }
+                    fder *= iJ;
+                };
+                T vL, gL, vR, gR;
+                flux(false, nbL, sigL, ijL, S0 - D0, Q0 - P0, tl, dl, hvL[q], hwL[q], vL, gL);
+                flux(true, nbR, sigR, ijR, S0 + D0, P0 + Q0, tr, dr, hvR[q], hwR[q], vR, gR);
+                // rows: e_L v_L + e_R v_R + d_R g_R - d_L g_L, even and odd parts
+                const T vs = vL + vR, vd = vR - vL, gs = gR + gL, gd = gR - gL;
+                T ye[HE], yo[HN > 0 ? HN : 1];
+#pragma unroll
+                for (int k = 0; k < HE; ++k) {
+                    T acc = T(0);
+#pragma unroll
+                    for (int m = 0; m < HE; ++m) acc += R.Ke[k][m] * ev[m];
+                    ye[k] = WJ * acc + (R.se[k] * vs + R.pe[k] * gs);
+                }
+#pragma unroll
+                for (int k = 0; k < HN; ++k) {
+                    T acc = T(0);
+#pragma unroll
+                    for (int m = 0; m < HN; ++m) acc += R.Ko[k][m] * od[m];
+                    yo[k] = WJ * acc + (R.so[k] * vd + R.qo[k] * gd);
+                }
+#pragma unroll
+                for (int k = 0; k < HN; ++k) {
+                    Y[d][q][ls][k * sd + lo] = ye[k] + yo[k];
+                    Y[d][q][ls][(N - 1 - k) * sd + lo] = ye[k] - yo[k];
+                }
+                if constexpr (N % 2) Y[d][q][ls][HN * sd + lo] = ye[HN];
+            }
+        }
+        if (rn < nr) fetch_lines(rn);
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int l = t + it * OT;
+            if (l >= nodes) continue;
+            const long long ge = (long long)e0 * N3 + l;
+            const T di = MODE == OP_CHEB ? c2 * dinv[ge] : T(0);
+#pragma unroll
+            for (int q = 0; q < RB; ++q) {
+                if (!alive(rq, q)) continue;
+                const long long g = base(rq, q) + ge;
+                const T acc = (&Y[0][q][0][0])[l] + (&Y[1][q][0][0])[l] + (&Y[2][q][0][0])[l];
+                if constexpr (MODE == OP_APPLY) {
+                    out[g] = acc;
+                } else if constexpr (MODE == OP_RESID) {
+                    out[g] = fv[q][it] - acc;
+                } else {
+                    const T z = (&U[q][0][0])[l];
+                    out[g] = z + (c1 * (z - pv[q][it]) + di * (fv[q][it] - acc));
+                }
+            }
+        }
+        rq = rn;
     }
-#undef OCT_GATHER
 }
 
 // grid (chunks of 256, nrhs): per-node kernels over one level's fields
 inline dim3 node_grid(long long ndof, int nrhs) { return dim3((unsigned)((ndof + 255) / 256), (unsigned)nrhs); }
 
-// r = f, z = 0, d = c0 D^-1 f (smoothing from a zero start)
+// z = c0 D^-1 f (the first smoothing iterate from a zero start)
 template <typename T>
-__global__ __launch_bounds__(256) void k_oct_start0(long long ndof, const RhsState* __restrict__ st,
-                                                    const T* __restrict__ f, T* __restrict__ r,
-                                                    T* __restrict__ z, T* __restrict__ d,
-                                                    const T* __restrict__ dinv, T c0) {
+__global__ __launch_bounds__(256) void k_oct_start(long long ndof, const RhsState* __restrict__ st,
+                                                   const T* __restrict__ f, T* __restrict__ z,
+                                                   const T* __restrict__ dinv, T c0) {
     const int rhs = blockIdx.y;
     if (st && !st[rhs].active) return;
     const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
     if (q >= ndof) return;
     const long long g = (long long)rhs * ndof + q;
-    const T fv = f[g];
-    r[g] = fv;
-    z[g] = T(0);
-    d[g] = c0 * dinv[q] * fv;
-}
-
-// d = c0 D^-1 r
-template <typename T>
-__global__ __launch_bounds__(256) void k_oct_dstart(long long ndof, const RhsState* __restrict__ st,
-                                                    const T* __restrict__ r, T* __restrict__ d,
-                                                    const T* __restrict__ dinv, T c0) {
-    const int rhs = blockIdx.y;
-    if (st && !st[rhs].active) return;
-    const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (q >= ndof) return;
-    const long long g = (long long)rhs * ndof + q;
-    d[g] = c0 * dinv[q] * r[g];
-}
-
-// z += d
-template <typename T>
-__global__ __launch_bounds__(256) void k_oct_add(long long ndof, const RhsState* __restrict__ st,
-                                                 const T* __restrict__ d, T* __restrict__ z) {
-    const int rhs = blockIdx.y;
-    if (st && !st[rhs].active) return;
-    const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (q >= ndof) return;
-    const long long g = (long long)rhs * ndof + q;
-    z[g] += d[g];
+    z[g] = c0 * dinv[q] * f[g];
 }
 
 // FP32 V-cycle under FP64 CG: the residual narrowed to FP32, the correction widened to FP64
@@ -758,11 +782,13 @@ struct Level {
     long long ndof = 0;
     std::vector<int> cells;               // tree cell of each element
     std::vector<double> Jh;               // half-widths, 3 per element
-    std::vector<int> fsh;                 // piece ranges: {first, first hanging} per element, + end
-    std::vector<Piece> ph;
+    std::vector<Face> fh;                 // six per element
+    std::vector<Piece> ph;                // an element's pieces face by face
     std::vector<double> diag;
     double* J = nullptr;
-    int* fstart = nullptr;
+    double* geo = nullptr;                // per element: 1 / J per axis, products of the other axes' J
+    float* geo32 = nullptr;
+    Face* faces = nullptr;
     Piece* pcs = nullptr;
     double* dinv = nullptr;
     float* dinv32 = nullptr;
@@ -771,6 +797,7 @@ struct Level {
     std::vector<double> Ideg;             // n_f x n_c
     int* par = nullptr;                   // mesh step: parent per fine element
     int* msel = nullptr;                  // per fine element and axis: table entry
+    int* hstart = nullptr;                // first hanging piece of each element, + end
     int* kstart = nullptr;                // per coarse element: its fine elements
     int* kids = nullptr;
     // smoother
@@ -787,7 +814,7 @@ struct dg_octree {
     int E[3];
     double lo[3], hi[3], h[3];
     int q = 4;
-    int rhs_per_block = 0;                // right-hand sides per operator work-group (1, 2, 4; 0 by degree)
+    int rhs_per_block = 0;                // right-hand sides an operator work-group takes at a time (0: default)
     dg_opts opts;
     std::vector<dg::oct::TCell> tree;
     int max_gen = 0;
@@ -814,7 +841,7 @@ struct dg_octree {
     dg::CoarseDev* cdev = nullptr;
     // work space (per right-hand-side capacity)
     int cap = 0;
-    std::vector<double*> wf, wz, wr, wd0, wd1, wt;
+    std::vector<double*> wf, wz, wy, wt;   // source, iterates (ping-pong), residual per level
     double* cscr = nullptr;
     double *px = nullptr, *pr = nullptr, *pz = nullptr, *pp = nullptr, *pq = nullptr;
     double* partial = nullptr;
@@ -1081,24 +1108,40 @@ void build_level(dg_octree& O, Level& L, bool finest) {
         O.bsh = bs;
         O.nbp = nbp;
     }
-    // per element: the conforming pieces and boundary faces, then the hanging pieces (each
-    // group face by face, a face's pieces by neighbour); fsh = {first, first hanging} per element
-    L.fsh.assign(2 * (size_t)L.ne + 1, 0);
+    // per element face its pieces by neighbour; a piece with identity entries only is the whole face of
+    // both sides, and the face's only one; the others are the device's list of hanging pieces
+    L.fh.clear();
     L.ph.clear();
+    std::vector<Piece> hanging;
+    std::vector<int> first(L.ne + 1, 0), hstart(L.ne + 1, 0);
     auto conforming = [](const Piece& p) { return p.s1 == 0 && p.s2 == 0 && p.n1 == 0 && p.n2 == 0; };
     for (int e = 0; e < L.ne; ++e) {
-        for (int fc = 0; fc < 6; ++fc)
-            std::sort(face[6 * e + fc].begin(), face[6 * e + fc].end(),
-                      [](const Piece& x, const Piece& y) { return x.nb < y.nb; });
-        L.fsh[2 * e] = (int)L.ph.size();
-        for (int hang = 0; hang < 2; ++hang) {
-            if (hang) L.fsh[2 * e + 1] = (int)L.ph.size();
-            for (int fc = 0; fc < 6; ++fc)
-                for (const Piece& p : face[6 * e + fc])
-                    if (conforming(p) != (hang == 1)) L.ph.push_back(p);
+        first[e] = (int)L.ph.size();
+        hstart[e] = (int)hanging.size();
+        for (int fc = 0; fc < 6; ++fc) {
+            auto& list = face[6 * e + fc];
+            std::sort(list.begin(), list.end(), [](const Piece& x, const Piece& y) { return x.nb < y.nb; });
+            for (Piece& p : list) {
+                p.el = e;
+                p.ij = 1.0 / L.Jh[3 * e + (fc >> 1)];
+            }
+            Face F{};
+            F.nb = -2;
+            F.first = (int)hanging.size();
+            F.count = (int)list.size();
+            if (F.count == 1 && conforming(list[0])) {
+                F.nb = list[0].nb;
+                F.sig = list[0].sig;
+                F.ijn = list[0].ijn;
+            } else {
+                hanging.insert(hanging.end(), list.begin(), list.end());
+            }
+            L.fh.push_back(F);
+            L.ph.insert(L.ph.end(), list.begin(), list.end());
         }
     }
-    L.fsh[2 * (size_t)L.ne] = (int)L.ph.size();
+    first[L.ne] = (int)L.ph.size();
+    hstart[L.ne] = (int)hanging.size();
     // diagonal: volume terms and, per piece, sum_q W T^2 sigma - kappa T d_n T (separable)
     std::vector<double> xi, w, D;
     node_rule(L.q, 1, xi, w, D);
@@ -1121,7 +1164,7 @@ void build_level(dg_octree& O, Level& L, bool finest) {
                 for (int i = 0; i < n; ++i)
                     De[(k * n + j) * n + i] = Jy * Jz / Jx * w[k] * w[j] * K1d[i] + Jx * Jz / Jy * w[k] * K1d[j] * w[i] +
                                               Jx * Jy / Jz * K1d[k] * w[j] * w[i];
-        for (int pi = L.fsh[2 * e]; pi < L.fsh[2 * e + 2]; ++pi) {
+        for (int pi = first[e]; pi < first[e + 1]; ++pi) {
             const Piece& P = L.ph[pi];
             const int fc = P.face;
             const int d = fc >> 1;
@@ -1164,8 +1207,18 @@ void build_level(dg_octree& O, Level& L, bool finest) {
     std::vector<double> dinv(L.ndof);
     for (long long q = 0; q < L.ndof; ++q) dinv[q] = 1.0 / L.diag[q];
     L.J = upload(L.Jh);
-    L.fstart = upload(L.fsh);
-    L.pcs = upload(L.ph);
+    L.faces = upload(L.fh);
+    std::vector<double> geo(6 * (size_t)L.ne);
+    for (int e = 0; e < L.ne; ++e)
+        for (int d = 0; d < 3; ++d) {
+            geo[6 * e + d] = 1.0 / L.Jh[3 * e + d];
+            geo[6 * e + 3 + d] = L.Jh[3 * e + (d + 1) % 3] * L.Jh[3 * e + (d + 2) % 3];
+        }
+    L.geo = upload(geo);
+    std::vector<float> geo32(geo.begin(), geo.end());
+    L.geo32 = upload(geo32);
+    L.pcs = upload(hanging);
+    L.hstart = upload(hstart);
     L.dinv = upload(dinv);
     std::vector<float> dinv32(dinv.begin(), dinv.end());
     L.dinv32 = upload(dinv32);
@@ -1209,49 +1262,87 @@ const double* dinv_of<double>(const Level& L) { return L.dinv; }
 template <>
 const float* dinv_of<float>(const Level& L) { return L.dinv32; }
 
+template <typename T>
+const T* geo_of(const Level& L);
+template <>
+const double* geo_of<double>(const Level& L) { return L.geo; }
+template <>
+const float* geo_of<float>(const Level& L) { return L.geo32; }
+
+// the reference data in the field type
+template <int N, typename T>
+OpRef<N, T> make_opref() {
+    const Ref<N> D = make_ref<N>(N - 1);
+    OpRef<N, T> R;
+    constexpr int H = N / 2, HE = (N + 1) / 2;
+    for (int i = 0; i < N; ++i) {
+        R.w[i] = (T)D.w[i];
+        R.eR[i] = (T)D.eR[i];
+        R.dR[i] = (T)D.dR[i];
+    }
+    // with x_i = (even + odd) / 2, x_(N-1-i) = (even - odd) / 2; row k is ye_k + yo_k, row N-1-k ye_k - yo_k
+    for (int k = 0; k < HE; ++k) {
+        const bool mid = k == H;
+        R.se[k] = (T)(mid ? D.eR[k] : 0.5 * (D.eR[k] + D.eR[N - 1 - k]));
+        R.pe[k] = (T)(mid ? D.dR[k] : 0.5 * (D.dR[k] + D.dR[N - 1 - k]));
+        for (int m = 0; m < HE; ++m)
+            R.Ke[k][m] = (T)(m == H ? D.K1[k][m] : 0.5 * (D.K1[k][m] + D.K1[k][N - 1 - m]));
+    }
+    for (int k = 0; k < H; ++k) {
+        R.so[k] = (T)(0.5 * (D.eR[k] - D.eR[N - 1 - k]));
+        R.qo[k] = (T)(0.5 * (D.dR[k] - D.dR[N - 1 - k]));
+        for (int m = 0; m < H; ++m) R.Ko[k][m] = (T)(0.5 * (D.K1[k][m] - D.K1[k][N - 1 - m]));
+    }
+    return R;
+}
+
 template <int N, int RB, typename T>
-void op_launch_nb(const dg_octree& O, const Level& L, int mode, int nrhs, const RhsState* st, const T* u, T* y,
-                  const T* f, T* r, T* z, double c1, double c2, hipStream_t s) {
-    constexpr int EPB = OT / (N * N * N);
-    static const Ref<N> R = make_ref<N>(N - 1);
-    dim3 grid((L.ne + EPB - 1) / EPB, (nrhs + RB - 1) / RB);
+void op_launch_nb(const dg_octree& O, const Level& L, int mode, int nrhs, const RhsState* st, const T* u,
+                  const T* uprev, const T* f, T* out, double c1, double c2, hipStream_t s) {
+    constexpr int EPB = op_epb(N);
+    static const OpRef<N, T> R = make_opref<N, T>();
+    // Right-hand sides a work-group takes in turn: longer chunks overlap more loads, but the launch should
+    // keep about OP_WGS work-groups (36 right-hand sides on 2,836 elements, N = 5, FP32: 1,024 245 us, 2,048 215,
+    // 3,000 190, 4,096 185, 6,000 194, 20,000 191 in an earlier form)
+    const int blocks = (L.ne + EPB - 1) / EPB;
+    const int parts = std::max(1, std::min((OP_WGS + blocks - 1) / blocks, (nrhs + RB - 1) / RB));
+    const int chunk = std::min(64, ((nrhs + parts - 1) / parts + RB - 1) / RB * RB);
+    dim3 grid(blocks, (nrhs + chunk - 1) / chunk);
     const T* tab = tab_of<T>(O, N);
     const T* dinv = dinv_of<T>(L);
+    const T* geo = geo_of<T>(L);
     if (mode == OP_APPLY)
-        hipLaunchKernelGGL((k_oct_op<N, OP_APPLY, RB, T>), grid, dim3(OT), 0, s, R, L.ne, nrhs, L.J, L.fstart, L.pcs,
-                           tab, st, u, y, f, r, z, dinv, (T)c1, (T)c2);
+        hipLaunchKernelGGL((k_oct_op<N, OP_APPLY, RB, T>), grid, dim3(OT), 0, s, R, L.ne, nrhs, chunk, geo, L.faces,
+                           L.hstart, L.pcs, tab, st, u, uprev, f, out, dinv, (T)c1, (T)c2);
     else if (mode == OP_RESID)
-        hipLaunchKernelGGL((k_oct_op<N, OP_RESID, RB, T>), grid, dim3(OT), 0, s, R, L.ne, nrhs, L.J, L.fstart, L.pcs,
-                           tab, st, u, y, f, r, z, dinv, (T)c1, (T)c2);
+        hipLaunchKernelGGL((k_oct_op<N, OP_RESID, RB, T>), grid, dim3(OT), 0, s, R, L.ne, nrhs, chunk, geo, L.faces,
+                           L.hstart, L.pcs, tab, st, u, uprev, f, out, dinv, (T)c1, (T)c2);
     else
-        hipLaunchKernelGGL((k_oct_op<N, OP_CHEB, RB, T>), grid, dim3(OT), 0, s, R, L.ne, nrhs, L.J, L.fstart, L.pcs,
-                           tab, st, u, y, f, r, z, dinv, (T)c1, (T)c2);
+        hipLaunchKernelGGL((k_oct_op<N, OP_CHEB, RB, T>), grid, dim3(OT), 0, s, R, L.ne, nrhs, chunk, geo, L.faces,
+                           L.hstart, L.pcs, tab, st, u, uprev, f, out, dinv, (T)c1, (T)c2);
 }
 
-// right-hand sides per work-group: several share the element's geometry, pieces and tables and
-// give each thread independent work between the barriers
+// right-hand sides at a time
 template <int N, typename T>
-void op_launch_n(const dg_octree& O, const Level& L, int mode, int nrhs, const RhsState* st, const T* u, T* y,
-                 const T* f, T* r, T* z, double c1, double c2, hipStream_t s) {
-    // 0: by type and degree, the fastest measured: four in FP32 and at degree 4 in FP64, else two
-    const int rb = O.rhs_per_block > 0 ? O.rhs_per_block : (sizeof(T) == 4 || N == 5 ? 4 : 2);
-    if (rb >= 4 && nrhs >= 4)
-        op_launch_nb<N, 4, T>(O, L, mode, nrhs, st, u, y, f, r, z, c1, c2, s);
-    else if (rb >= 2 && nrhs >= 2)
-        op_launch_nb<N, 2, T>(O, L, mode, nrhs, st, u, y, f, r, z, c1, c2, s);
+void op_launch_n(const dg_octree& O, const Level& L, int mode, int nrhs, const RhsState* st, const T* u,
+                 const T* uprev, const T* f, T* out, double c1, double c2, hipStream_t s) {
+    const int rb = O.rhs_per_block > 0 ? O.rhs_per_block : 2;
+    if (rb >= 2 && nrhs >= 2)
+        op_launch_nb<N, 2, T>(O, L, mode, nrhs, st, u, uprev, f, out, c1, c2, s);
     else
-        op_launch_nb<N, 1, T>(O, L, mode, nrhs, st, u, y, f, r, z, c1, c2, s);
+        op_launch_nb<N, 1, T>(O, L, mode, nrhs, st, u, uprev, f, out, c1, c2, s);
 }
 
+// out = A u, f - A u or a Chebyshev step (see k_oct_op)
 template <typename T>
-void op_launch(const dg_octree& O, const Level& L, int mode, int nrhs, const RhsState* st, const T* u, T* y,
-               const T* f, T* r, T* z, double c1, double c2, hipStream_t s) {
+void op_launch(const dg_octree& O, const Level& L, int mode, int nrhs, const RhsState* st, const T* u,
+               const T* uprev, const T* f, T* out, double c1, double c2, hipStream_t s) {
     if (nrhs == 0 || L.ne == 0) return;
     switch (L.n) {
-        case 2: op_launch_n<2, T>(O, L, mode, nrhs, st, u, y, f, r, z, c1, c2, s); break;
-        case 3: op_launch_n<3, T>(O, L, mode, nrhs, st, u, y, f, r, z, c1, c2, s); break;
-        case 4: op_launch_n<4, T>(O, L, mode, nrhs, st, u, y, f, r, z, c1, c2, s); break;
-        case 5: op_launch_n<5, T>(O, L, mode, nrhs, st, u, y, f, r, z, c1, c2, s); break;
+        case 2: op_launch_n<2, T>(O, L, mode, nrhs, st, u, uprev, f, out, c1, c2, s); break;
+        case 3: op_launch_n<3, T>(O, L, mode, nrhs, st, u, uprev, f, out, c1, c2, s); break;
+        case 4: op_launch_n<4, T>(O, L, mode, nrhs, st, u, uprev, f, out, c1, c2, s); break;
+        case 5: op_launch_n<5, T>(O, L, mode, nrhs, st, u, uprev, f, out, c1, c2, s); break;
         default: throw std::invalid_argument("octree operator: degree 1 to 4");
     }
 }
@@ -1301,9 +1392,7 @@ void ensure_work(dg_octree& O, int nrhs) {
     };
     fr(O.wf);
     fr(O.wz);
-    fr(O.wr);
-    fr(O.wd0);
-    fr(O.wd1);
+    fr(O.wy);
     fr(O.wt);
     ofree(O.cscr);
     ofree(O.px);
@@ -1316,9 +1405,7 @@ void ensure_work(dg_octree& O, int nrhs) {
         const long long n = L.ndof * nrhs;
         O.wf.push_back(oalloc<double>(n));
         O.wz.push_back(oalloc<double>(n));
-        O.wr.push_back(oalloc<double>(n));
-        O.wd0.push_back(oalloc<double>(n));
-        O.wd1.push_back(oalloc<double>(n));
+        O.wy.push_back(oalloc<double>(n));
         O.wt.push_back(oalloc<double>(n));
     }
     O.cscr = oalloc<double>(2LL * nrhs * O.lv.back().ndof);
@@ -1346,31 +1433,9 @@ void ensure_state(dg_octree& O, int nrhs) {
     O.st_cap = nrhs;
 }
 
-// Chebyshev smoothing of level l on f from z (zero_start: z = 0), the work vectors of the level
-// (the FP64 buffers hold FP32 values in their first half when T is float)
-template <typename T>
-void smooth(dg_octree& O, int l, int nrhs, const RhsState* st, const T* f, T* z, bool zero_start, hipStream_t s) {
-    const Level& L = O.lv[l];
-    T* r = reinterpret_cast<T*>(O.wr[l]);
-    T* d0 = reinterpret_cast<T*>(O.wd0[l]);
-    T* d1 = reinterpret_cast<T*>(O.wd1[l]);
-    const T* dinv = dinv_of<T>(L);
-    if (zero_start) {
-        hipLaunchKernelGGL((k_oct_start0<T>), node_grid(L.ndof, nrhs), dim3(256), 0, s, L.ndof, st, f, r, z, d0, dinv,
-                           (T)L.c0);
-    } else {
-        op_launch<T>(O, L, OP_RESID, nrhs, st, z, r, f, nullptr, nullptr, 0.0, 0.0, s);
-        hipLaunchKernelGGL((k_oct_dstart<T>), node_grid(L.ndof, nrhs), dim3(256), 0, s, L.ndof, st, r, d0, dinv,
-                           (T)L.c0);
-    }
-    for (int k = 1; k < L.degree; ++k) {
-        op_launch<T>(O, L, OP_CHEB, nrhs, st, d0, d1, nullptr, r, z, L.cp[k - 1], L.cr[k - 1], s);
-        std::swap(d0, d1);
-    }
-    hipLaunchKernelGGL((k_oct_add<T>), node_grid(L.ndof, nrhs), dim3(256), 0, s, L.ndof, st, d0, z);
-}
-
-// z = V f on level l (f is not modified)
+// z = V f on level l (f is not modified).  The iterates alternate between the level's second buffer and z,
+// an odd number of times, so the last one is in z.  (The FP64 buffers hold FP32 values in their first half
+// when T is float.)
 template <typename T>
 void vcycle(dg_octree& O, int l, int nrhs, const RhsState* st, const T* f, T* z, hipStream_t s) {
     const int nl = (int)O.lv.size();
@@ -1382,12 +1447,23 @@ void vcycle(dg_octree& O, int l, int nrhs, const RhsState* st, const T* f, T* z,
     T* t = reinterpret_cast<T*>(O.wt[l]);
     T* fc = reinterpret_cast<T*>(O.wf[l + 1]);
     T* zc = reinterpret_cast<T*>(O.wz[l + 1]);
-    smooth<T>(O, l, nrhs, st, f, z, true, s);
-    op_launch<T>(O, L, OP_RESID, nrhs, st, z, t, f, nullptr, nullptr, 0.0, 0.0, s);
+    T *cur = reinterpret_cast<T*>(O.wy[l]), *prev = z;
+    hipLaunchKernelGGL((k_oct_start<T>), node_grid(L.ndof, nrhs), dim3(256), 0, s, L.ndof, st, f, cur, dinv_of<T>(L),
+                       (T)L.c0);
+    for (int k = 1; k < L.degree; ++k) {
+        op_launch<T>(O, L, OP_CHEB, nrhs, st, cur, k == 1 ? nullptr : prev, f, prev, L.cp[k - 1], L.cr[k - 1],
+                     s);
+        std::swap(cur, prev);
+    }
+    op_launch<T>(O, L, OP_RESID, nrhs, st, cur, nullptr, f, t, 0.0, 0.0, s);
     transfer<T>(O, l, true, nrhs, st, t, fc, s);
     vcycle<T>(O, l + 1, nrhs, st, fc, zc, s);
-    transfer<T>(O, l, false, nrhs, st, zc, z, s);
-    smooth<T>(O, l, nrhs, st, f, z, false, s);
+    transfer<T>(O, l, false, nrhs, st, zc, cur, s);
+    for (int k = 0; k < L.degree; ++k) {
+        op_launch<T>(O, L, OP_CHEB, nrhs, st, cur, k == 0 ? nullptr : prev, f, prev, k == 0 ? 0.0 : L.cp[k - 1],
+                     k == 0 ? L.c0 : L.cr[k - 1], s);
+        std::swap(cur, prev);
+    }
 }
 
 // the preconditioner z = V r at the finest level in the solve's V-cycle precision
@@ -1433,7 +1509,7 @@ void lanczos_bounds(dg_octree& O, int l, hipStream_t s) {
     const int steps = (int)std::min<long long>(O.opts.lanczos_steps, n);
     for (int k = 0; k < steps; ++k) {
         hipLaunchKernelGGL(k_oct_dscale, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, L.dinv, v, tmp);
-        op_launch<double>(O, L, OP_APPLY, 1, nullptr, tmp, w, nullptr, nullptr, nullptr, 0.0, 0.0, s);
+        op_launch<double>(O, L, OP_APPLY, 1, nullptr, tmp, nullptr, nullptr, w, 0.0, 0.0, s);
         hipLaunchKernelGGL(k_oct_dscale, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, L.dinv, w, w);
         launch_axpby(n, -beta, vp, 1.0, w, s);
         const double alpha = dot(w, v);
@@ -1498,7 +1574,10 @@ void destroy(dg_octree* O) {
     (void)hipSetDevice(O->device);
     for (Level& L : O->lv) {
         ofree(L.J);
-        ofree(L.fstart);
+        ofree(L.faces);
+        ofree(L.hstart);
+        ofree(L.geo);
+        ofree(L.geo32);
         ofree(L.pcs);
         ofree(L.dinv);
         ofree(L.dinv32);
@@ -1522,7 +1601,7 @@ void destroy(dg_octree* O) {
     ofree(O->xpi);
     ofree(O->xpj);
     ofree(O->cdev);
-    for (auto* v : {&O->wf, &O->wz, &O->wr, &O->wd0, &O->wd1, &O->wt})
+    for (auto* v : {&O->wf, &O->wz, &O->wy, &O->wt})
         for (auto& p : *v) ofree(p);
     ofree(O->cscr);
     ofree(O->px);
@@ -1802,13 +1881,13 @@ void boundary_data(dg_octree* O, int nsrc, const double* f, double* g, hipStream
 
 void apply(dg_octree* O, int level, int nrhs, const double* u, double* y, hipStream_t s) {
     if (level < 0 || level >= (int)O->lv.size()) throw std::invalid_argument("level out of range");
-    op_launch<double>(*O, O->lv[level], OP_APPLY, nrhs, nullptr, u, y, nullptr, nullptr, nullptr, 0.0, 0.0, s);
+    op_launch<double>(*O, O->lv[level], OP_APPLY, nrhs, nullptr, u, nullptr, nullptr, y, 0.0, 0.0, s);
     OCHK(hipGetLastError());
 }
 
 void apply_f32(dg_octree* O, int level, int nrhs, const float* u, float* y, hipStream_t s) {
     if (level < 0 || level >= (int)O->lv.size()) throw std::invalid_argument("level out of range");
-    op_launch<float>(*O, O->lv[level], OP_APPLY, nrhs, nullptr, u, y, nullptr, nullptr, nullptr, 0.0, 0.0, s);
+    op_launch<float>(*O, O->lv[level], OP_APPLY, nrhs, nullptr, u, nullptr, nullptr, y, 0.0, 0.0, s);
     OCHK(hipGetLastError());
 }
 
@@ -1848,7 +1927,7 @@ int solve(dg_octree* O, int nrhs, const double* b, double* x, dg_rhs_stats* stat
             launch_dot<double, double>(n, nrhs, st, O->pr, O->pz, O->partial, O->pstride, s);
             launch_finalize(FIN_RZ, nrhs, st, O->partial, O->pstride, nc, s);
             hipLaunchKernelGGL(k_oct_pdir, node_grid(n, nrhs), dim3(256), 0, s, n, st, O->pz, O->pp);
-            op_launch<double>(*O, L, OP_APPLY, nrhs, st, O->pp, O->pq, nullptr, nullptr, nullptr, 0.0, 0.0, s);
+            op_launch<double>(*O, L, OP_APPLY, nrhs, st, O->pp, nullptr, nullptr, O->pq, 0.0, 0.0, s);
             launch_dot<double, double>(n, nrhs, st, O->pp, O->pq, O->partial, O->pstride, s);
             launch_finalize(FIN_PQ, nrhs, st, O->partial, O->pstride, nc, s);
             hipLaunchKernelGGL(k_oct_xr, node_grid(n, nrhs), dim3(256), 0, s, n, st, O->pp, O->pq, x, O->pr);
@@ -1863,7 +1942,7 @@ int solve(dg_octree* O, int nrhs, const double* b, double* x, dg_rhs_stats* stat
     }
     OCHK(hipGetLastError());
     // FP64 residual of the returned solution
-    op_launch<double>(*O, L, OP_RESID, nrhs, nullptr, x, O->pr, b, nullptr, nullptr, 0.0, 0.0, s);
+    op_launch<double>(*O, L, OP_RESID, nrhs, nullptr, x, nullptr, b, O->pr, 0.0, 0.0, s);
     launch_dot<double, double>(n, nrhs, nullptr, O->pr, O->pr, O->partial, O->pstride, s);
     std::vector<double> part((size_t)nrhs * O->pstride);
     OCHK(hipMemcpyAsync(part.data(), O->partial, sizeof(double) * part.size(), hipMemcpyDeviceToHost, s));

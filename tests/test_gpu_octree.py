@@ -75,6 +75,28 @@ def test_refined_mesh_matches_oracle(gpu_lib, case):
     print(f"case {case}: {g.n_elements} elements, {g.n_dofs} nodes, generations {t.max_gen}, {g.n_levels} levels")
 
 
+@pytest.mark.parametrize("q,nrhs,rb", [(4, 1, 0), (4, 3, 2), (3, 67, 0), (2, 130, 4), (1, 5, 1)])
+def test_operator_work_group_edges_match_oracle(gpu_lib, q, nrhs, rb):
+    """A sharp density beside a face of an unrefined base cell: coarse faces tiled by more hanging pieces
+    than a work-group takes at once, level jumps beyond the interpolation tables it keeps in LDS; one
+    right-hand side, an odd count, and counts beyond a work-group's 64."""
+    ne, lo, hi = (2, 1, 1), (-2.0, -1.0, -1.0), (2.0, 1.0, 1.0)
+    rho = _gauss(60.0, (0.25, 0.1, -0.2))
+    g = gpu_lib.Octree(ne, lo, hi, q=q, rho=rho, delta_q=1e-6, max_depth=4)
+    m = octree.Octree(ne, lo, hi, q, rho=rho, delta_q=1e-6, max_depth=4).mesh()
+    assert g.n_elements == len(m.cells)
+    if rb:
+        g.set_rhs_per_block(rb)
+    rng = np.random.default_rng(q)
+    u = rng.standard_normal((nrhs, g.n_dofs))
+    y = g.apply(_t(u)).cpu().numpy().reshape(nrhs, -1)
+    some = sorted({0, nrhs - 1, min(nrhs - 1, 64), nrhs // 2})
+    ref = np.stack([m.apply(u[k]) for k in some])
+    assert np.abs(y[some] - ref).max() <= 1e-12 * np.abs(ref).max()
+    y32 = g.apply_f32(_t(u).float()).cpu().numpy().reshape(nrhs, -1)
+    assert np.abs(y32[some] - ref).max() <= 2e-5 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("case", CASES)
 def test_operator_rhs_bounds_and_vcycle_match_oracle(gpu_lib, case):
     g, t = _pair(gpu_lib, case)
