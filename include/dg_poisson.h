@@ -323,11 +323,13 @@ dg_status dg_ace_action(dg_ctx* ctx, int mesh_id, int nbasis, const double* phi,
                         const double* xi, double* out, hipStream_t stream);
 
 /* Work-group tiles of the operator kernels (host only; no GPU needed).
- * The operator steps of the path run as a slab kernel on nodes-per-edge n = 2,
- * 3 and 5 (degrees 1, 2, 4): a work-group owns tx x ty elements of the x-y
- * plane and zlen element layers along z.  dg_tile_set chooses the tile of one
- * step (DG_STEP_*) for one arithmetic (fp_bytes 4: FP32, 8: FP64) and one n,
- * for every context set up afterwards (contexts set up before keep theirs).
+ * The operator steps of the path run as a slab kernel: a work-group owns
+ * tx x ty elements of the x-y plane and up to zlen element layers along z
+ * (fewer where the batch has too little work to fill the GPU).  dg_tile_set
+ * chooses the tile of one step (DG_STEP_*) for one arithmetic (fp_bytes 4:
+ * FP32, 8: FP64) and nodes-per-edge n = 2, 3 or 5 (degrees 1, 2, 4) of
+ * Gauss-Lobatto levels, for every context set up afterwards (contexts set up
+ * before keep theirs); the other degrees' tiles are fixed (dg_tile_get: tx = 0).
  * Compiled shapes: n = 2: 8x8, zlen 1..2; n = 3: 4x4, zlen 1..4; n = 5: 4x2,
  * 4x4 or 2x2, zlen 1..4; anything else returns DG_ERR_ARG.  dg_tile_get
  * reports the current choice (host outputs).  The built-in defaults are

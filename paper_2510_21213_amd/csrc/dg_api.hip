@@ -125,7 +125,7 @@ struct dg_ctx {
         // 4: BF16F_PC)
         struct Graph {
             hipGraphExec_t exec = nullptr;
-            int nrhs = 0, every = 0;
+            int nrhs = 0, every = 0, wgs = 0;
             bool prof = false;
             std::vector<hipEvent_t> ev;
             size_t nev = 0;
@@ -364,7 +364,7 @@ int lp_fields(const dg_ctx* ctx, const Mesh& M) {
     auto degree_step = [](const LevelHost& F, const LevelHost& C, int nf, int nc) {
         return F.n == nf && C.n == nc && !F.hcoarse && F.E[0] == C.E[0] && F.E[1] == C.E[1] && F.E[2] == C.E[2];
     };
-    if (!degree_step(M.lv[0], M.lv[1], 5, 3) || !dg::has_pq_mixed(M.lv[0])) return 0;
+    if (M.lv[0].family != 0 || !degree_step(M.lv[0], M.lv[1], 5, 3) || !dg::has_pq_mixed(M.lv[0])) return 0;
     return M.lv.size() >= 3 && degree_step(M.lv[1], M.lv[2], 3, 2) ? 2 : 1;
 }
 
@@ -620,7 +620,7 @@ void pcg_run(dg_ctx* ctx, Mesh& M, Work<T>& W, int nrhs, dg::RhsState* st, const
         int every = std::max(2, ctx->opts.check_every);
         every += every & 1;
         auto& G = M.graph[kind];
-        if (!G.exec || G.nrhs != nrhs || G.every != every || G.prof != timed) {
+        if (!G.exec || G.nrhs != nrhs || G.every != every || G.wgs != L0.wgs || G.prof != timed) {
             if (G.exec) (void)hipGraphExecDestroy(G.exec);
             G.exec = nullptr;
             size_t used = 0;
@@ -653,6 +653,7 @@ void pcg_run(dg_ctx* ctx, Mesh& M, Work<T>& W, int nrhs, dg::RhsState* st, const
             HIPCHK(e);
             G.nrhs = nrhs;
             G.every = every;
+            G.wgs = L0.wgs;
             G.prof = timed;
             G.nev = used;
         }
@@ -1166,6 +1167,9 @@ void add_jobs(dg_ctx* ctx, int mesh_id, int cnt, const double* b, const double* 
 // lane's stream from its own host thread (the host waits of one overlap the kernels of
 // the others).  Results do not depend on how the jobs are run.
 void run_jobs(dg_ctx* ctx, std::vector<Job>& jobs, hipStream_t stream) {
+    const int wgs = dg::slab_wgs((int)jobs.size());
+    for (auto& J : jobs)
+        for (auto& L : J.M->lv) L.wgs = wgs;
     if (jobs.size() == 1) {
         auto& J = jobs[0];
         solve_group(ctx, *J.M, J.cnt, J.b, J.x0, J.v, J.stats, stream, J.guard);
@@ -1234,9 +1238,6 @@ void setup_mesh(dg_ctx* ctx, const dg_mesh& mesh, Mesh& M, hipStream_t s) {
         L.family = o.node_family;
         for (int d = 0; d < 3; ++d) L.nbr[d] = (E[d] + L.be - 1) / L.be;
         dg::assign_tiles(L);
-        if (L.family != 0)  // the slab kernels take face values at the end nodes: GL runs on the bricks
-            for (int f = 0; f < 2; ++f)
-                for (int m = 0; m <= dg::BM_RESTRICT; ++m) L.tile[f][m][0] = 0;
         for (int d = 0; d < 3; ++d) {
             dg::build_axis(E[d], p, mesh.lo[d], mesh.hi[d], o.penalty_eps, L.d64.ax[d], nullptr, nullptr, L.family);
             auto& a = L.d64.ax[d];
@@ -1260,7 +1261,7 @@ void setup_mesh(dg_ctx* ctx, const dg_mesh& mesh, Mesh& M, hipStream_t s) {
             f.E = a.E;
             f.gl = a.gl;
         }
-        dg::build_ref(p, o.penalty_eps, L.h, L.d64.ref);
+        dg::build_ref(p, o.penalty_eps, L.h, L.d64.ref, L.family);
         {
             const auto& r = L.d64.ref;
             auto& f = L.d32.ref;
@@ -1269,6 +1270,7 @@ void setup_mesh(dg_ctx* ctx, const dg_mesh& mesh, Mesh& M, hipStream_t s) {
                 for (int j = 0; j < dg::NMAX; ++j) f.B[i][j] = (float)r.B[i][j];
                 f.aL[i] = (float)r.aL[i];
                 f.aR[i] = (float)r.aR[i];
+                f.eL[i] = (float)r.eL[i];
                 f.w[i] = (float)r.w[i];
             }
             f.sig = (float)r.sig;

@@ -47,6 +47,7 @@ template <typename T>
 struct RefDev {
     T B[NMAX][NMAX];
     T aL[NMAX], aR[NMAX];
+    T eL[NMAX];  // line -> value at the left end of the element (the first node for GLL); eR_l = eL_{p-l}
     T w[NMAX];
     T sig;
     T scale[3];
@@ -122,8 +123,9 @@ struct LevelHost {
     int nbr[3];      // bricks per axis
     int be;          // elements per brick edge
     // slab-kernel tile per arithmetic (0 FP32, 1 FP64) and operator step (BrickMode):
-    // {tx, ty, zlen}; tx = 0 selects the brick kernel.  Fixed when the level is set up.
+    // {tx, ty, longest chunk}; tx = 0 selects the brick kernel.  Fixed when the level is set up.
     int tile[2][7][3];
+    int wgs = 576;  // work-groups a launch should have before its chunks grow to their full length (slab_wgs)
 };
 
 // Host-side numerics (dg_setup.cpp).
@@ -136,7 +138,7 @@ void lagrange_deriv(const std::vector<double>& nodes, const std::vector<double>&
 void jacobi_eigen(int n, std::vector<double>& A, std::vector<double>& lam, std::vector<double>& V);
 void build_axis(int E, int p, double lo, double hi, double eps, AxisDev<double>& ax, std::vector<double>* dense,
                 std::vector<double>* nodes, int family = 0);
-void build_ref(int p, double eps, const double h[3], RefDev<double>& r);
+void build_ref(int p, double eps, const double h[3], RefDev<double>& r, int family = 0);
 int brick_edge(int n);
 std::vector<std::pair<std::array<int, 3>, int>> hierarchy(const int E[3], int p, int n_levels);
 void build_transfer(const LevelHost& fine, const LevelHost& coarse, TransferDev& tr);

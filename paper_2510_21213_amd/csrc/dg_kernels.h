@@ -49,6 +49,8 @@ void assign_tiles(LevelHost& L);
 // `mode` (its work-groups per right-hand side).
 template <typename T>
 int op_blocks(const LevelHost& L, int mode);
+// LevelHost.wgs for solves of which `jobs` run at the same time.  Results do not depend on it.
+int slab_wgs(int jobs);
 
 template <typename T>
 void launch_brick(int mode, const LevelHost& L, const LevelDev<T>* dev, int nrhs, const RhsState* st, const T* u,

@@ -13,14 +13,14 @@
 // and for the left neighbour (value up and derivative dp at its right end)
 //     y_e += e_L ( dp/2 - sigma up) - d_L (up/2).
 //
-// Tiling.  The operator kernels of degrees 1, 2 and 4 (every level of the benchmark
-// hierarchies) are slab kernels (k_slab): a work-group owns a TX x TY tile of elements in the
+// Tiling.  The operator kernels of degrees 1 to 6, on both node families, are slab kernels
+// (k_slab): a work-group owns a TX x TY tile of elements in the
 // x-y plane of one right-hand side and marches along z through a chunk of element layers; per
 // layer it stages the tile and its ring of x/y neighbour elements in LDS, computes the x and y
 // terms of element pairs in two thread halves at once and the z term of each node column in
 // registers (the previous and next layers supply the z neighbours, so no z halo is read), and
-// applies the step's epilogue (Chebyshev update, residual, search direction, restriction).  The
-// other degrees (3, 5, 6, 7) use the earlier brick kernel (k_brick): a BE^3-element brick staged
+// applies the step's epilogue (Chebyshev update, residual, search direction, restriction).
+// Degree 7 uses the brick kernel (k_brick): a BE^3-element brick staged
 // in LDS, neighbour lines outside it read from global memory.  Work-group indices are remapped
 // so that each XCD receives a contiguous range of tiles.
 //
@@ -517,7 +517,9 @@ struct SlabArgs {
 // Coefficients of the interior block in the even/odd form of RefDev (symmetric
 // and invariant under the reflection of the reference element; aR_l = -aL_{p-l}):
 // 17 scalars for p = 4, held in scalar registers for the whole work-group.
-template <typename T, int N>
+// GL: Gauss-Legendre nodes, where the values at the ends of an element are eL . A and
+// eR . A (eR_l = eL_{p-l}) instead of its end nodes.
+template <typename T, int N, bool GL = false>
 struct SlabCoef {
     static constexpr int H = N / 2;
     T Pe[H][H], Po[H][H];
@@ -525,11 +527,16 @@ struct SlabCoef {
     T qe[H], qo[H], qm;
     T aL[N];
     T sig;
+    T eL[GL ? N : 1];
 };
 
-template <typename T, int N>
-__device__ __forceinline__ void load_coef(SlabCoef<T, N>& c, const RefDev<T>& R) {
+template <typename T, int N, bool GL>
+__device__ __forceinline__ void load_coef(SlabCoef<T, N, GL>& c, const RefDev<T>& R) {
     constexpr int H = N / 2;
+    if constexpr (GL) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) c.eL[i] = R.eL[i];
+    }
 #pragma unroll
     for (int i = 0; i < H; ++i) {
 #pragma unroll
@@ -548,18 +555,44 @@ __device__ __forceinline__ void load_coef(SlabCoef<T, N>& c, const RefDev<T>& R)
     c.sig = R.sig;
 }
 
-template <typename T, int N>
-__device__ __forceinline__ T face_l(const SlabCoef<T, N>& c, const T* v) {
+// The slab kernels leave no contraction to the compiler: the z loop is unrolled, and each copy must
+// round alike, or a node's value would depend on its layer's place in a chunk (and so on the batch).
+__device__ __forceinline__ float fm(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fm(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+template <typename T, int N, bool GL>
+__device__ __forceinline__ T face_l(const SlabCoef<T, N, GL>& c, const T* v) {
+#pragma clang fp contract(off)
     T s = 0;
 #pragma unroll
-    for (int l = 0; l < N; ++l) s += c.aL[l] * v[l];
+    for (int l = 0; l < N; ++l) s = fm(c.aL[l], v[l], s);
     return s;
 }
-template <typename T, int N>
-__device__ __forceinline__ T face_r(const SlabCoef<T, N>& c, const T* v) {
+template <typename T, int N, bool GL>
+__device__ __forceinline__ T face_r(const SlabCoef<T, N, GL>& c, const T* v) {
+#pragma clang fp contract(off)
     T s = 0;
 #pragma unroll
-    for (int l = 0; l < N; ++l) s -= c.aL[N - 1 - l] * v[l];
+    for (int l = 0; l < N; ++l) s = fm(-c.aL[N - 1 - l], v[l], s);
+    return s;
+}
+// values of an element's line at its left and right ends
+template <typename T, int N, bool GL>
+__device__ __forceinline__ T end_l(const SlabCoef<T, N, GL>& c, const T* v) {
+#pragma clang fp contract(off)
+    if constexpr (!GL) return v[0];
+    T s = 0;
+#pragma unroll
+    for (int l = 0; l < N; ++l) s = fm(c.eL[GL ? l : 0], v[l], s);
+    return s;
+}
+template <typename T, int N, bool GL>
+__device__ __forceinline__ T end_r(const SlabCoef<T, N, GL>& c, const T* v) {
+#pragma clang fp contract(off)
+    if constexpr (!GL) return v[N - 1];
+    T s = 0;
+#pragma unroll
+    for (int l = 0; l < N; ++l) s = fm(c.eL[GL ? N - 1 - l : 0], v[l], s);
     return s;
 }
 
@@ -569,15 +602,18 @@ __device__ __forceinline__ T face_r(const SlabCoef<T, N>& c, const T* v) {
 //   acc_i += (aR_i U0 - aL_i U) / 2,  acc_0 += Dv/2 - sig U,  acc_p -= D0/2 + sig U0.
 // With the ghost data U = -A_0, Dv = aL.A - 2 sig A_0 on a left domain face and
 // U0 = -A_p, D0 = aR.A + 2 sig A_p on a right one, the same formula gives the
-// block of a boundary element (its Nitsche face terms).
+// block of a boundary element (its Nitsche face terms).  On Gauss-Legendre nodes the
+// values A_0, A_p above are eL . A, eR . A and the jump terms Dv/2 - sig U and
+// -(D0/2 + sig U0) are tested with eL_i and eR_i at every node.
 //
 // B is invariant under the reflection of the reference element and aR_i =
 // -aL_{p-i}, so the rows i and p-i are computed together from the even and odd
 // parts of A (ue = A_l + A_{p-l}, uo = A_l - A_{p-l}) and of the coupling
 // (S = U0 + U, D = U0 - U): acc_i, acc_{p-i} = ev_i +- od_i (32 operations per
 // element at p = 4 instead of 41).
-template <typename T, int N>
-__device__ __forceinline__ void elem_op(const SlabCoef<T, N>& c, const T* A, T U, T Dv, T U0, T D0, T* acc) {
+template <typename T, int N, bool GL>
+__device__ __forceinline__ void elem_op(const SlabCoef<T, N, GL>& c, const T* A, T U, T Dv, T U0, T D0, T* acc) {
+#pragma clang fp contract(off)
     constexpr int H = N / 2;
     constexpr bool ODD = (N & 1) != 0;
     const T S = U0 + U, D = U0 - U;
@@ -588,26 +624,34 @@ __device__ __forceinline__ void elem_op(const SlabCoef<T, N>& c, const T* A, T U
         uo[l] = A[l] - A[N - 1 - l];
     }
     if constexpr (ODD) ue[H] = A[H];
+    const T X0 = fm((T)0.5, Dv, -(c.sig * U)), X1 = fm((T)0.5, D0, c.sig * U0);
 #pragma unroll
     for (int i = 0; i < H; ++i) {
         T ev = c.qe[i] * S, od = c.qo[i] * D;
+        if constexpr (GL) {
+            ev = fm((T)0.5 * (c.eL[GL ? i : 0] + c.eL[GL ? N - 1 - i : 0]), X0 - X1, ev);
+            od = fm((T)0.5 * (c.eL[GL ? i : 0] - c.eL[GL ? N - 1 - i : 0]), X0 + X1, od);
+        }
 #pragma unroll
         for (int l = 0; l < H; ++l) {
-            ev += c.Pe[i][l] * ue[l];
-            od += c.Po[i][l] * uo[l];
+            ev = fm(c.Pe[i][l], ue[l], ev);
+            od = fm(c.Po[i][l], uo[l], od);
         }
-        if constexpr (ODD) ev += c.Bm[i] * ue[H];
+        if constexpr (ODD) ev = fm(c.Bm[i], ue[H], ev);
         acc[i] = ev + od;
         acc[N - 1 - i] = ev - od;
     }
     if constexpr (ODD) {
         T m = c.qm * S;
+        if constexpr (GL) m = fm(c.eL[GL ? H : 0], X0 - X1, m);
 #pragma unroll
-        for (int l = 0; l <= H; ++l) m += c.Bm[l] * ue[l];
+        for (int l = 0; l <= H; ++l) m = fm(c.Bm[l], ue[l], m);
         acc[H] = m;
     }
-    acc[0] += (T)0.5 * Dv - c.sig * U;
-    acc[N - 1] -= (T)0.5 * D0 + c.sig * U0;
+    if constexpr (!GL) {
+        acc[0] += X0;
+        acc[N - 1] -= X1;
+    }
 }
 
 // x or y term of the element pair (e, e+1) of a row staged in LDS at su[pb +
@@ -616,9 +660,10 @@ __device__ __forceinline__ void elem_op(const SlabCoef<T, N>& c, const T* A, T U
 // exist are replaced by ghost data and their lines are not used.  The
 // results, times sc, go to so[ob + s OSTR], s in [0, 2N) (the second element
 // only if it exists).
-template <typename T, int N, int PSTR, int OSTR>
-__device__ __forceinline__ void pair_row(const SlabCoef<T, N>& c, const T* su, int pb, T* so, int ob, int e, int nE,
+template <typename T, int N, int PSTR, int OSTR, bool GL>
+__device__ __forceinline__ void pair_row(const SlabCoef<T, N, GL>& c, const T* su, int pb, T* so, int ob, int e, int nE,
                                          T sc) {
+#pragma clang fp contract(off)
     T A[N], B[N], out[N];
 #pragma unroll
     for (int l = 0; l < N; ++l) {
@@ -626,24 +671,24 @@ __device__ __forceinline__ void pair_row(const SlabCoef<T, N>& c, const T* su, i
         B[l] = su[pb + (2 * N + l) * PSTR];
     }
     const bool has2 = e + 1 < nE;
-    const T fRA = face_r(c, A);
+    const T fRA = face_r(c, A), vRA = end_r(c, A);
     T U, Dv, U0, D0;
     if (e > 0) {
         T nl[N];
 #pragma unroll
         for (int l = 0; l < N; ++l) nl[l] = su[pb + l * PSTR];
-        U = nl[N - 1];
+        U = end_r(c, nl);
         Dv = face_r(c, nl);
     } else {
-        U = -A[0];
-        Dv = face_l(c, A) - (T)2 * c.sig * A[0];
+        U = -end_l(c, A);
+        Dv = fm((T)2 * c.sig, U, face_l(c, A));
     }
     if (has2) {
-        U0 = B[0];
+        U0 = end_l(c, B);
         D0 = face_l(c, B);
     } else {
-        U0 = -A[N - 1];
-        D0 = fRA + (T)2 * c.sig * A[N - 1];
+        U0 = -vRA;
+        D0 = fm((T)2 * c.sig, vRA, fRA);
     }
     elem_op(c, A, U, Dv, U0, D0, out);
 #pragma unroll
@@ -653,13 +698,13 @@ __device__ __forceinline__ void pair_row(const SlabCoef<T, N>& c, const T* su, i
             T nr[N];
 #pragma unroll
             for (int l = 0; l < N; ++l) nr[l] = su[pb + (3 * N + l) * PSTR];
-            U0 = nr[0];
+            U0 = end_l(c, nr);
             D0 = face_l(c, nr);
         } else {
-            U0 = -B[N - 1];
-            D0 = face_r(c, B) + (T)2 * c.sig * B[N - 1];
+            U0 = -end_r(c, B);
+            D0 = fm((T)2 * c.sig, -U0, face_r(c, B));
         }
-        elem_op(c, B, A[N - 1], fRA, U0, D0, out);
+        elem_op(c, B, vRA, fRA, U0, D0, out);
 #pragma unroll
         for (int i = 0; i < N; ++i) so[ob + (N + i) * OSTR] = out[i] * sc;
     }
@@ -728,6 +773,7 @@ __device__ __forceinline__ float from_bf16(__bf16 h) {
 // the product of exactly the direction that is stored).
 template <typename T, int N, int MODE, typename S = T, typename ZP = float, typename SP = S>
 __device__ __forceinline__ void load_col(T* v, brsrc ru, brsrc ru2, uint32_t voff, uint32_t soff, T beta) {
+#pragma clang fp contract(off)
     if constexpr (MODE == BM_PQ32) {
         static_assert(sizeof(T) == 8 && sizeof(S) == 8, "BM_PQ32 is an FP64 step");
         constexpr uint32_t R = sizeof(T) / sizeof(ZP);
@@ -746,7 +792,7 @@ __device__ __forceinline__ void load_col(T* v, brsrc ru, brsrc ru2, uint32_t vof
         for (int k = 0; k < N; ++k) {
             T w;
             fload<S>(w, ru2, voff, soff + k * N * N * (uint32_t)sizeof(S));
-            v[k] += beta * w;
+            v[k] = fm(beta, w, v[k]);
         }
     } else if constexpr (MODE == BM_PQ32) {
         constexpr uint32_t R2 = sizeof(T) / sizeof(SP);
@@ -754,7 +800,7 @@ __device__ __forceinline__ void load_col(T* v, brsrc ru, brsrc ru2, uint32_t vof
         for (int k = 0; k < N; ++k) {
             T w;
             fload<SP>(w, ru2, voff / R2, soff / R2 + k * N * N * (uint32_t)sizeof(SP));
-            v[k] += beta * w;
+            v[k] = fm(beta, w, v[k]);
             if constexpr (sizeof(SP) == 4) v[k] = (T)(float)v[k];
         }
     }
@@ -803,6 +849,7 @@ __device__ __forceinline__ float mf_coef(const RefDev<float>& R, int i, int k) {
 template <int N, int TX, int TY>
 __device__ __forceinline__ void mf_ghosts(const SlabCoef<float, N>& c, float* su, int tx0, int ty0, int E0,
                                           int E1) {
+#pragma clang fp contract(off)
     constexpr int NX = TX * N, NY = TY * N, RS = NX + 2 * N, PS = RS * (NY + 2 * N);
     const int nvx = min(TX, E0 - tx0), nvy = min(TY, E1 - ty0);  // valid elements of the tile per axis
     const bool lx = tx0 == 0, rx = tx0 + TX >= E0, ly = ty0 == 0, ry = ty0 + TY >= E1;
@@ -835,13 +882,13 @@ __device__ __forceinline__ void mf_ghosts(const SlabCoef<float, N>& c, float* su
 #pragma unroll
         for (int l = 0; l < N; ++l) g[l] = 0.f;
         if (!side) {  // left ghost: U = -A_0, Dv = aL.A - 2 sig A_0; g = (g0, 0, ..., 0, U)
-            const float U = -A[0], Dv = face_l(c, A) - 2.f * c.sig * A[0];
+            const float U = -A[0], Dv = fm(-2.f * c.sig, A[0], face_l(c, A));
             g[N - 1] = U;
-            g[0] = -(Dv + c.aL[0] * U) / c.aL[N - 1];
+            g[0] = -fm(c.aL[0], U, Dv) / c.aL[N - 1];
         } else {      // right ghost: U0 = -A_p, D0 = aR.A + 2 sig A_p; g = (U0, 0, ..., 0, gp)
-            const float U0 = -A[N - 1], D0 = face_r(c, A) + 2.f * c.sig * A[N - 1];
+            const float U0 = -A[N - 1], D0 = fm(2.f * c.sig, A[N - 1], face_r(c, A));
             g[0] = U0;
-            g[N - 1] = (D0 - c.aL[0] * U0) / c.aL[N - 1];
+            g[N - 1] = fm(-c.aL[0], U0, D0) / c.aL[N - 1];
         }
         const int gpos = side ? first + N : first - N;
 #pragma unroll
@@ -902,13 +949,24 @@ __device__ __forceinline__ void mf_xy_terms(const RefDev<float>& R, const mf_s4&
     }
 }
 
+// Waves per SIMD that the registers are held to where the compiler meets the count or misses it by a
+// few: six (80 VGPRs) for the FP32 smoothing steps of degree 4 on 4x2 tiles (at 81, five waves: 36
+// right-hand sides of 16^3 elements in BF16F_PC 17.6 ms, at 80 16.9), three (168) for the FP64 ones.
+template <typename T, int N, int TX, int TY, int MODE, bool MF, bool GL>
+constexpr int slab_waves() {
+    if (N != 5 || TY != 2 || MF || GL) return 1;
+    if (sizeof(T) == 4) return TX == 4 && MODE == BM_CHEB ? 6 : 1;
+    return TX == 2 && (MODE == BM_CHEB || MODE == BM_CHEBDOT) ? 3 : 1;
+}
+
 // S: storage type of the fields u, u2, f, zprev, out, out2 (T, or BF16 for FP32 arithmetic; the
 // pointers of SlabArgs<T> then address BF16 data); ZP: type of the BM_PQ32 input uf; SP: storage
 // type of the BM_PQ32 search direction (u2 in, out2 out); SC: storage type of the BM_RESTRICT
 // outputs fc and z1c (the coarse level's source and first smoothing iterate).
 template <typename T, int N, int TX, int TY, int MODE, bool MF = false, typename S = T, typename ZP = float,
-          typename SP = S, typename SC = T>
-__global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
+          typename SP = S, typename SC = T, bool GL = false>
+__global__ __launch_bounds__(wg_of(TX* TY* N* N), (slab_waves<T, N, TX, TY, MODE, MF, GL>())) void k_slab(SlabArgs<T> a) {
+#pragma clang fp contract(off)
     constexpr int NX = TX * N, NY = TY * N, NT = NX * NY, N2 = N * N, N3 = N2 * N;
     constexpr int WG = wg_of(NT);
     constexpr int RS = NX + 2 * N, PS = RS * (NY + 2 * N);  // LDS staging: row and plane strides
@@ -930,7 +988,8 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
     __shared__ T su[N * PS];
     __shared__ T sr[MODE == BM_RESTRICT ? NC * OP : 1];  // BM_RESTRICT: residual contracted along z
     __shared__ T sxy[2 * N * OP];
-    __shared__ double red[WG / 64];
+    constexpr int ZMAX = slab_zmax(N);  // longest chunk (tile_compiled)
+    __shared__ double red[DOT ? ZMAX : 1][WG / 64];
 
     const int per_rhs = a.nt0 * a.nt1 * a.nzc;
     const int w = xcd_remap(blockIdx.x, per_rhs * a.nrhs);
@@ -969,7 +1028,7 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
     const bool has_zp = IS_CHEB && a.zprev;
 
     const RefDev<T>& R = a.L->ref;
-    SlabCoef<T, N> c;
+    SlabCoef<T, N, GL> c;
     load_coef(c, R);
     mf_s4 mfA = {0, 0, 0, 0};
     if constexpr (MF) {
@@ -996,11 +1055,18 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
     T P1 = 0;                           // x and y parts of the diagonal (times w_k)
     if constexpr (IS_CHEB) {
         T bdx = R.B[i][i], bdy = R.B[j][j];
-        if (ex == 0 && i == 0) bdx += R.aL[0];
-        if (ex == E0 - 1 && i == N - 1) bdx -= R.aR[N - 1];
-        if (ey == 0 && j == 0) bdy += R.aL[0];
-        if (ey == E1 - 1 && j == N - 1) bdy -= R.aR[N - 1];
-        P1 = R.scale[0] * bdx * wj + R.scale[1] * wi * bdy;
+        if constexpr (GL) {  // diag of the boundary block: eL_i aL_i more at a left face, mirrored at a right one
+            if (ex == 0) bdx = fm(R.eL[i], R.aL[i], bdx);
+            if (ex == E0 - 1) bdx = fm(R.eL[N - 1 - i], R.aL[N - 1 - i], bdx);
+            if (ey == 0) bdy = fm(R.eL[j], R.aL[j], bdy);
+            if (ey == E1 - 1) bdy = fm(R.eL[N - 1 - j], R.aL[N - 1 - j], bdy);
+        } else {
+            if (ex == 0 && i == 0) bdx += R.aL[0];
+            if (ex == E0 - 1 && i == N - 1) bdx -= R.aR[N - 1];
+            if (ey == 0 && j == 0) bdy += R.aL[0];
+            if (ey == E1 - 1 && j == N - 1) bdy -= R.aR[N - 1];
+        }
+        P1 = fm(R.scale[0] * bdx, wj, R.scale[1] * wi * bdy);
     }
     // halo role: the same node (i, j) of halo element he = el + s TX TY
     uint32_t hoff[HS];
@@ -1056,7 +1122,7 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
     T prevU = 0, prevD = 0;
     if (ezb > 0) {
         load_col<T, N, MODE, S, ZP, SP>(nx2, ru, ru2, coff, (uint32_t)(ezb - 1) * lstride, beta);
-        prevU = nx2[N - 1];
+        prevU = end_r(c, nx2);
         prevD = face_r(c, nx2);
     }
     load_col<T, N, MODE, S, ZP, SP>(cur, ru, ru2, coff, (uint32_t)ezb * lstride, beta);
@@ -1067,13 +1133,12 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
     T crD[N], crD0 = 0, crDN = 0;
     if constexpr (IS_CHEB) {
 #pragma unroll
-        for (int k = 0; k < N; ++k) crD[k] = a.cr * recip(P1 * R.w[k] + P2 * R.B[k][k]);
-        crD0 = a.cr * recip(P1 * R.w[0] + P2 * (R.B[0][0] + R.aL[0]));
-        crDN = a.cr * recip(P1 * R.w[N - 1] + P2 * (R.B[N - 1][N - 1] - R.aR[N - 1]));
+        for (int k = 0; k < N; ++k) crD[k] = a.cr * recip(fm(P1, R.w[k], P2 * R.B[k][k]));
+        crD0 = a.cr * recip(fm(P1, R.w[0], P2 * (R.B[0][0] + R.aL[0])));
+        crDN = a.cr * recip(fm(P1, R.w[N - 1], P2 * (R.B[N - 1][N - 1] - R.aR[N - 1])));
     }
 
-    double dot = 0.0;
-    constexpr int ZMAX = slab_zmax(N);  // longest chunk (tile_compiled)
+    double dots[DOT ? ZMAX : 1] = {};
 #pragma unroll
     for (int zq = 0; zq < ZMAX; ++zq) {
         const int ez = ezb + zq;
@@ -1135,19 +1200,19 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
                 U = prevU;
                 Dv = prevD;
             } else {
-                U = -cur[0];
-                Dv = face_l(c, cur) - (T)2 * c.sig * cur[0];
+                U = -end_l(c, cur);
+                Dv = fm((T)2 * c.sig, U, face_l(c, cur));
             }
-            const T fRc = face_r(c, cur);
+            const T fRc = face_r(c, cur), vRc = end_r(c, cur);
             if (ez + 1 < E2) {
-                U0 = nxt[0];
+                U0 = end_l(c, nxt);
                 D0 = face_l(c, nxt);
             } else {
-                U0 = -cur[N - 1];
-                D0 = fRc + (T)2 * c.sig * cur[N - 1];
+                U0 = -vRc;
+                D0 = fm((T)2 * c.sig, vRc, fRc);
             }
             elem_op(c, cur, U, Dv, U0, D0, zacc);
-            prevU = cur[N - 1];
+            prevU = vRc;
             prevD = fRc;
         }
         __syncthreads();
@@ -1159,31 +1224,40 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
         if (colok) {
 #pragma unroll
             for (int k = 0; k < N; ++k) {
-                const T y = zacc[k] * P2 + sxy[k * OP + so_own] + sxy[N * OP + k * OP + so_own];
+                const T y = fm(zacc[k], P2, sxy[k * OP + so_own]) + sxy[N * OP + k * OP + so_own];
                 const uint32_t so = soff + k * N2 * SZ;
                 if constexpr (MODE == BM_APPLY) {
                     fstore<S>(y, ro, coff, so);
                 } else if constexpr (MODE == BM_RESID || MODE == BM_RESIDDOT) {
                     const T r = fcol[k] - y;
                     fstore<S>(r, ro, coff, so);
-                    if constexpr (MODE == BM_RESIDDOT) dot += (double)r * (double)r;
+                    if constexpr (MODE == BM_RESIDDOT) dots[zq] = fm((double)r, (double)r, dots[zq]);
                 } else if constexpr (IS_CHEB) {
                     T cd = crD[k];
-                    if (k == 0 && ez == 0) cd = crD0;
-                    if (k == N - 1 && ez == E2 - 1) cd = crDN;
+                    if constexpr (GL) {
+                        if (ez == 0 || ez == E2 - 1) {
+                            T bd = R.B[k][k];
+                            if (ez == 0) bd = fm(R.eL[k], R.aL[k], bd);
+                            if (ez == E2 - 1) bd = fm(R.eL[N - 1 - k], R.aL[N - 1 - k], bd);
+                            cd = a.cr * recip(fm(P1, R.w[k], P2 * bd));
+                        }
+                    } else {
+                        if (k == 0 && ez == 0) cd = crD0;
+                        if (k == N - 1 && ez == E2 - 1) cd = crDN;
+                    }
                     const T uz = cur[k];
-                    const T zn = uz + a.cp * (uz - zpcol[k]) + cd * (fcol[k] - y);
+                    const T zn = fm(cd, fcol[k] - y, fm(a.cp, uz - zpcol[k], uz));
                     fstore<S>(zn, ro, coff, so);
-                    if constexpr (MODE == BM_CHEBDOT) dot += (double)fcol[k] * (double)zn;
+                    if constexpr (MODE == BM_CHEBDOT) dots[zq] = fm((double)fcol[k], (double)zn, dots[zq]);
                 } else if constexpr (MODE == BM_PQ32) {
                     constexpr uint32_t R2 = sizeof(T) / sizeof(SP);
                     fstore<SP>(cur[k], ro2, coff / R2, so / R2);
                     fstore<S>(y, ro, coff, so);
-                    dot += (double)cur[k] * (double)y;
+                    dots[zq] = fm((double)cur[k], (double)y, dots[zq]);
                 } else if constexpr (IS_PQ) {
                     fstore<S>(cur[k], ro2, coff, so);
                     fstore<S>(y, ro, coff, so);
-                    dot += (double)cur[k] * (double)y;
+                    dots[zq] = fm((double)cur[k], (double)y, dots[zq]);
                 } else if constexpr (MODE == BM_RESTRICT) {
                     rr[k] = fcol[k] - y;
                 }
@@ -1204,7 +1278,7 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
                 for (int cc = 0; cc < NC; ++cc) {
                     T s = 0;
 #pragma unroll
-                    for (int k = 0; k < N; ++k) s += Pm(k, cc) * rr[k];
+                    for (int k = 0; k < N; ++k) s = fm(Pm(k, cc), rr[k], s);
                     sr[cc * OP + so_own] = s;
                 }
             }
@@ -1221,8 +1295,8 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
                 for (int jj = 0; jj < N; ++jj) {
                     T u = 0;
 #pragma unroll
-                    for (int i = 0; i < N; ++i) u += pa[i] * sr[cz * OP + (eyl2 * N + jj) * OR + exl2 * N + i];
-                    s += Pm(jj, cb) * u;
+                    for (int i = 0; i < N; ++i) u = fm(pa[i], sr[cz * OP + (eyl2 * N + jj) * OR + exl2 * N + i], u);
+                    s = fm(Pm(jj, cb), u, s);
                 }
                 const long long idx =
                     (long long)rhs * a.ndofc + ((long long)(ez * E1 + eyo) * E0 + exo) * NC3 + loc;
@@ -1244,9 +1318,24 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N)) void k_slab(SlabArgs<T> a) {
             nxt[k] = nx2[k];
         }
     }
+    // one partial sum per tile and element layer, whatever the chunks: a right-hand side's sums are
+    // then the same bits in every batch, though the chunk length follows the size of the batch
     if constexpr (DOT) {
-        const double s = block_sum<WG>(dot, red);
-        if (t == 0) a.partial[(long long)rhs * a.pstride + slot] = s;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int q = 0; q < ZMAX; ++q) dots[q] += __shfl_xor(dots[q], o, 64);
+        if ((t & 63) == 0) {
+#pragma unroll
+            for (int q = 0; q < ZMAX; ++q) red[q][t >> 6] = dots[q];
+        }
+        __syncthreads();
+        if (t < eze - ezb) {
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < WG / 64; ++w) s += red[t][w];
+            a.partial[(long long)rhs * a.pstride + (long long)(ezb + t) * (a.nt0 * a.nt1) + tile] = s;
+        }
     }
 }
 
@@ -1289,7 +1378,23 @@ static void default_tile(int fp64, int n, int mode, int& tx, int& ty, int& zlen)
     }
 }
 
-// The shapes launch_slab has kernels for.
+// Tiles of the levels that tile_set does not choose: n = 4, 6 and 7, and every Gauss-Legendre level
+// (n <= 7, the same shapes).  Measured, whole solves: n = 4 (FP32_PC) 8^3 elements x 4 right-hand sides
+// 1.60 ms on 4x2 tiles, 1.65 on 4x4, and 16^3 x 16 6.52 and 6.39, so 4x4 from 1000 elements; FP64 4^3
+// x 1 1.57 and 1.66, 12x14x10 x 8 4.86 and 4.88.  n = 6 (10x14x12 x 5, FP32_PC) 6.85 ms on 2x2,
+// 7.33 on 4x2; n = 7 (6x6x7 x 2) 2.86 ms on 2x2 against 3.17 on the bricks.  n = 8 stays on the bricks:
+// its seven N-vectors a thread leave a 2x2 tile one wave per SIMD (8^3 x 12, FP32_PC 10.8 ms against 7.3).
+static void fixed_tile(int fp64, const LevelHost& L, int mode, int& tx, int& ty, int& zlen) {
+    default_tile(fp64, L.n, mode, tx, ty, zlen);
+    if (L.n == 4) {
+        tx = 4;
+        ty = !fp64 && (long long)L.E[0] * L.E[1] * L.E[2] >= 1000 ? 4 : 2;
+    }
+    if (L.n == 6 || L.n == 7) tx = ty = 2;
+    if (L.n == 5 && L.family) ty = 2;
+}
+
+// The shapes tile_set may choose.
 static bool tile_compiled(int n, int tx, int ty, int zlen) {
     if (zlen < 1 || zlen > slab_zmax(n)) return false;
     switch (n) {
@@ -1346,7 +1451,8 @@ void assign_tiles(LevelHost& L) {
     for (int f = 0; f < 2; ++f)
         for (int m = 0; m <= BM_RESTRICT; ++m) {
             int* t = L.tile[f][m];
-            if (L.n < 2 || L.n > 8 || !tile_get(f ? 8 : 4, L.n, m, &t[0], &t[1], &t[2])) t[0] = t[1] = 0, t[2] = 4;
+            if (L.family || L.n == 4 || L.n >= 6 || !tile_get(f ? 8 : 4, L.n, m, &t[0], &t[1], &t[2]))
+                fixed_tile(f, L, m, t[0], t[1], t[2]);
         }
 }
 
@@ -1354,8 +1460,20 @@ struct SlabGeom {
     int tx, ty, nt0, nt1, zlen, nzc;
 };
 
+// A chunk reads its first layer's neighbour once more than it must, but a work-group passes its layers
+// one after the other: below about two work-groups per CU the launch takes as long as one chunk, and
+// short chunks win.  Whole solves, p = 4, chunks of the table's 4 layers (2 at degree 1) against this
+// rule (576 work-groups): 4x5x6 elements x 1 right-hand side 3.56 -> 1.99 ms, 16^3 x 1 FP64 5.69 -> 4.23, 16^3 x 4 6.05 ->
+// 5.08, 12x10x14 x 16 6.19 -> 5.58.  With more work-groups than that the reads count: at 512, 640, 1024
+// and 2048 16^3 x 4 takes 5.42, 5.08, 5.04 and 5.16 ms, and 16^3 x 36 with one layer a chunk 20.5
+// against 16.9.  Solves that run at the same time fill the GPU together: two lanes of a mesh overlap
+// only in part and keep the whole target each (10x14x12 p = 5 and 8^3 Gauss-Legendre cases: 6.87 and
+// 10.9 ms, 7.70 and 12.5 at 256), six meshes of 4^3 to 14^3 at once (96 right-hand sides) take 28.3 ms
+// at 576 and 28.0 at 256 and with full chunks.
+int slab_wgs(int jobs) { return std::min(576, 1152 / std::max(1, jobs)); }
+
 template <typename T>
-static SlabGeom slab_geom(const LevelHost& L, int mode) {
+static SlabGeom slab_geom(const LevelHost& L, int mode, int nrhs) {
     SlabGeom g;
     const int* t = L.tile[sizeof(T) == 8][mode == BM_PQ32 ? BM_PQ : mode];
     g.tx = t[0];
@@ -1365,37 +1483,47 @@ static SlabGeom slab_geom(const LevelHost& L, int mode) {
     g.nt0 = (L.E[0] + g.tx - 1) / g.tx;
     g.nt1 = (L.E[1] + g.ty - 1) / g.ty;
     g.zlen = std::min(g.zlen, L.E[2]);
+    // shorter chunks until wgs work-groups (slab_wgs)
+    while (g.zlen > 1 && (long long)g.nt0 * g.nt1 * ((L.E[2] + g.zlen - 1) / g.zlen) * nrhs < L.wgs)
+        g.zlen = (g.zlen + 1) / 2;
     g.nzc = (L.E[2] + g.zlen - 1) / g.zlen;
     return g;
 }
 
 template <typename T>
 int op_blocks(const LevelHost& L, int mode) {
-    const SlabGeom g = slab_geom<T>(L, mode);
-    return g.tx ? g.nt0 * g.nt1 * g.nzc : bricks_of(L);
+    const SlabGeom g = slab_geom<T>(L, mode, 1);
+    return g.tx ? g.nt0 * g.nt1 * L.E[2] : bricks_of(L);
 }
 template int op_blocks<float>(const LevelHost&, int);
 template int op_blocks<double>(const LevelHost&, int);
 
-template <typename T, int N, int TX, int TY>
+template <typename T, int N, int TX, int TY, bool GL = false>
 static void slab_dispatch(int mode, const SlabArgs<T>& a, int grid, hipStream_t s) {
     constexpr int WG = wg_of(TX * TY * N * N);
+#define DG_SLAB(MODE)                                                                                              \
+    case MODE:                                                                                                     \
+        hipLaunchKernelGGL((k_slab<T, N, TX, TY, MODE, false, T, float, T, T, GL>), dim3(grid), dim3(WG), 0, s, a); \
+        break;
     switch (mode) {
-        case BM_APPLY: hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_APPLY>), dim3(grid), dim3(WG), 0, s, a); break;
-        case BM_RESID: hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_RESID>), dim3(grid), dim3(WG), 0, s, a); break;
-        case BM_CHEB: hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_CHEB>), dim3(grid), dim3(WG), 0, s, a); break;
-        case BM_CHEBDOT: hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_CHEBDOT>), dim3(grid), dim3(WG), 0, s, a); break;
-        case BM_PQ: hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_PQ>), dim3(grid), dim3(WG), 0, s, a); break;
-        case BM_RESIDDOT: hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_RESIDDOT>), dim3(grid), dim3(WG), 0, s, a); break;
+        DG_SLAB(BM_APPLY)
+        DG_SLAB(BM_RESID)
+        DG_SLAB(BM_CHEB)
+        DG_SLAB(BM_CHEBDOT)
+        DG_SLAB(BM_PQ)
+        DG_SLAB(BM_RESIDDOT)
         case BM_RESTRICT:
-            if constexpr (N == 3 || N == 5)
-                hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_RESTRICT>), dim3(grid), dim3(WG), 0, s, a);
+            if constexpr (N > 2)
+                hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_RESTRICT, false, T, float, T, T, GL>), dim3(grid), dim3(WG),
+                                   0, s, a);
             break;
         case BM_PQ32:
             if constexpr (sizeof(T) == 8)
-                hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_PQ32>), dim3(grid), dim3(WG), 0, s, a);
+                hipLaunchKernelGGL((k_slab<T, N, TX, TY, BM_PQ32, false, T, float, T, T, GL>), dim3(grid), dim3(WG), 0,
+                                   s, a);
             break;
     }
+#undef DG_SLAB
 }
 
 // The BF16-field forms: FP32 arithmetic on BF16 fields (smoothing, smoothing with f.z, restriction,
@@ -1435,14 +1563,31 @@ static void slab_dispatch_lp(int mode, const SlabArgs<T>& a, int grid, hipStream
     }
 }
 
+// The tiles of fixed_tile.
+template <typename T, bool GL>
+static bool slab_fixed(int mode, int n, const SlabGeom& g, const SlabArgs<T>& a, int grid, hipStream_t s) {
+    constexpr int TX5 = sizeof(T) == 8 ? 2 : 4;
+    if constexpr (GL) {
+        if (g.tx == 8 && g.ty == 8 && n == 2) return slab_dispatch<T, 2, 8, 8, GL>(mode, a, grid, s), true;
+        if (g.tx == 4 && g.ty == 4 && n == 3) return slab_dispatch<T, 3, 4, 4, GL>(mode, a, grid, s), true;
+        if (g.tx == TX5 && g.ty == 2 && n == 5) return slab_dispatch<T, 5, TX5, 2, GL>(mode, a, grid, s), true;
+    }
+    if constexpr (sizeof(T) == 4)
+        if (g.tx == 4 && g.ty == 4 && n == 4) return slab_dispatch<T, 4, 4, 4, GL>(mode, a, grid, s), true;
+    if (g.tx == 4 && g.ty == 2 && n == 4) return slab_dispatch<T, 4, 4, 2, GL>(mode, a, grid, s), true;
+    if (g.tx == 2 && g.ty == 2 && n == 6) return slab_dispatch<T, 6, 2, 2, GL>(mode, a, grid, s), true;
+    if (g.tx == 2 && g.ty == 2 && n == 7) return slab_dispatch<T, 7, 2, 2, GL>(mode, a, grid, s), true;
+    return false;
+}
+
 template <typename T>
 static bool launch_slab(int mode, const LevelHost& L, const LevelDev<T>* dev, int nrhs, const RhsState* st,
                         const T* u, const T* u2, const T* f, const T* zprev, T* out, T* out2, double* partial,
                         int pstride, double cp, double cr, hipStream_t s, const LevelHost* Lc = nullptr,
                         const LevelDev<T>* devc = nullptr, T* fc = nullptr, T* z1c = nullptr, double c0c = 0,
                         const void* uf = nullptr, bool mf = false, bool lp = false, bool lpc = false) {
-    SlabGeom g = slab_geom<T>(L, mode);
-    if (mf && mode == BM_APPLY && L.n == 5) {  // no partial sums: the smoothing steps' 4 x 2 tile, 4 layers
+    SlabGeom g = slab_geom<T>(L, mode, nrhs);
+    if (mf && mode == BM_APPLY && L.n == 5 && L.family == 0) {  // no partial sums: the smoothing steps' 4 x 2 tile, 4 layers
         g.tx = 4;
         g.ty = 2;
         g.nt0 = (L.E[0] + 3) / 4;
@@ -1452,10 +1597,10 @@ static bool launch_slab(int mode, const LevelHost& L, const LevelDev<T>* dev, in
     }
     if (!g.tx) return false;
     // the matrix-core form exists for FP32 fields of degree 4 on 4 x 2 tiles
-    if (mf && !(sizeof(T) == 4 && L.n == 5 && g.tx == 4 && g.ty == 2 &&
+    if (mf && !(sizeof(T) == 4 && L.n == 5 && L.family == 0 && g.tx == 4 && g.ty == 2 &&
                 (mode == BM_APPLY || mode == BM_CHEB || mode == BM_CHEBDOT)))
         return false;
-    if (mode == BM_RESTRICT && L.n != 3 && L.n != 5) return false;
+    if (mode == BM_RESTRICT && L.n == 2) return false;  // mesh steps have no slab form
     SlabArgs<T> a;
     a.Lc = devc;
     a.tr = L.devtr;
@@ -1493,6 +1638,7 @@ static bool launch_slab(int mode, const LevelHost& L, const LevelDev<T>* dev, in
             return true;
         }
     }
+    if (lp && L.family) return false;
     if (lp) {  // BF16 fields: FP32 smoothing and restriction steps (degree 4 and 2), or the FP64 BM_PQ32 step
         if constexpr (sizeof(T) == 4) {
             if (L.n == 5) {
@@ -1516,12 +1662,13 @@ static bool launch_slab(int mode, const LevelHost& L, const LevelDev<T>* dev, in
         else return false;
         return true;
     }
+    if (L.family) return slab_fixed<T, true>(mode, L.n, g, a, grid, s);
     if (g.tx == 8 && g.ty == 8 && L.n == 2) slab_dispatch<T, 2, 8, 8>(mode, a, grid, s);
     else if (g.tx == 4 && g.ty == 4 && L.n == 3) slab_dispatch<T, 3, 4, 4>(mode, a, grid, s);
     else if (g.tx == 4 && g.ty == 2 && L.n == 5) slab_dispatch<T, 5, 4, 2>(mode, a, grid, s);
     else if (g.tx == 4 && g.ty == 4 && L.n == 5) slab_dispatch<T, 5, 4, 4>(mode, a, grid, s);
     else if (g.tx == 2 && g.ty == 2 && L.n == 5) slab_dispatch<T, 5, 2, 2>(mode, a, grid, s);
-    else return false;
+    else return slab_fixed<T, false>(mode, L.n, g, a, grid, s);
     return true;
 }
 
@@ -1544,15 +1691,8 @@ void launch_brick(int mode, const LevelHost& L, const LevelDev<T>* dev, int nrhs
     a.cr = (T)cr;
     const int grid = bricks_of(L) * nrhs;
     if (grid == 0) return;
-    switch (L.n) {
-        case 2: brick_dispatch<T, 2, be_of<2>()>(mode, a, grid, s); break;
-        case 3: brick_dispatch<T, 3, be_of<3>()>(mode, a, grid, s); break;
-        case 4: brick_dispatch<T, 4, be_of<4>()>(mode, a, grid, s); break;
-        case 5: brick_dispatch<T, 5, be_of<5>()>(mode, a, grid, s); break;
-        case 6: brick_dispatch<T, 6, be_of<6>()>(mode, a, grid, s); break;
-        case 7: brick_dispatch<T, 7, be_of<7>()>(mode, a, grid, s); break;
-        case 8: brick_dispatch<T, 8, be_of<8>()>(mode, a, grid, s); break;
-    }
+    if (L.n != 8) throw std::logic_error("launch_brick: no operator kernel for this degree");
+    brick_dispatch<T, 8, be_of<8>()>(mode, a, grid, s);
 }
 
 bool launch_brick_mf(int mode, const LevelHost& L, const LevelDev<float>* dev, int nrhs, const RhsState* st,
@@ -1582,7 +1722,7 @@ __global__ __launch_bounds__(256) void k_widen(const float* __restrict__ a, doub
     if (i < n) b[i] = (double)a[i];
 }
 
-bool has_pq_mixed(const LevelHost& L) { return slab_geom<double>(L, BM_PQ).tx != 0; }
+bool has_pq_mixed(const LevelHost& L) { return slab_geom<double>(L, BM_PQ, 1).tx != 0; }
 
 void launch_pq_mixed(const LevelHost& L, const LevelDev<double>* dev, int nrhs, const RhsState* st, const float* z,
                      const double* pold, double* q, double* pnew, double* tmp, double* partial, int pstride,
@@ -1845,14 +1985,16 @@ static TransferArgs<T> transfer_args(const LevelHost& Lf, const LevelHost& Lc, i
     return a;
 }
 
+// MACRO(fine n, coarse n, mesh step, has a form with an iterate): the slab kernel takes the degree
+// steps with an iterate, except from n = 8
 #define DG_TRANSFER_CASES(MACRO) \
-    MACRO(8, 4, false)           \
-    MACRO(7, 4, false)           \
-    MACRO(6, 3, false)           \
-    MACRO(5, 3, false)           \
-    MACRO(4, 2, false)           \
-    MACRO(3, 2, false)           \
-    MACRO(2, 2, true)
+    MACRO(8, 4, false, true)     \
+    MACRO(7, 4, false, false)    \
+    MACRO(6, 3, false, false)    \
+    MACRO(5, 3, false, false)    \
+    MACRO(4, 2, false, false)    \
+    MACRO(3, 2, false, false)    \
+    MACRO(2, 2, true, true)
 
 template <typename T>
 void launch_restrict(const LevelHost& Lf, const LevelDev<T>* devf, const LevelHost& Lc, const LevelDev<T>* devc,
@@ -1868,12 +2010,12 @@ void launch_restrict(const LevelHost& Lf, const LevelDev<T>* devf, const LevelHo
     const int grid = bricks_of(Lf) * nrhs;
     if (grid == 0) return;
     const bool hc = Lf.hcoarse;
-#define DG_R(NF, NC, HC)                                                                                         \
-    if (Lf.n == NF && Lc.n == NC && hc == HC) {                                                                 \
+#define DG_R(NF, NC, HC, WITHZ)                                                                                  \
+    if (Lf.n == NF && Lc.n == NC && hc == HC && (WITHZ || !z)) {                                                \
         constexpr int BE = be_of<NF>();                                                                         \
         constexpr int WG = wg_of(NF * BE * NF * BE);                                                            \
         if (z)                                                                                                  \
-            hipLaunchKernelGGL((k_restrict<T, NF, BE, NC, HC, true>), dim3(grid), dim3(WG), 0, s, a);           \
+            hipLaunchKernelGGL((k_restrict<T, NF, BE, NC, HC, WITHZ>), dim3(grid), dim3(WG), 0, s, a);          \
         else                                                                                                    \
             hipLaunchKernelGGL((k_restrict<T, NF, BE, NC, HC, false>), dim3(grid), dim3(WG), 0, s, a);          \
         return;                                                                                                 \
@@ -2019,23 +2161,19 @@ void launch_prolong(const LevelHost& Lf, const LevelHost& Lc, int nrhs, const Rh
         }
         DG_PD(5, 3)
         DG_PD(3, 2)
+        DG_PD(4, 2)
+        DG_PD(6, 3)
+        DG_PD(7, 4)
+        DG_PD(8, 4)
 #undef DG_PD
     }
+    if (!Lf.hcoarse || Lf.n != 2 || Lc.n != 2) throw std::logic_error("launch_prolong: no kernel for this step");
     TransferArgs<T> a = transfer_args<T>(Lf, Lc, nrhs, st);
     a.z = zc; a.zf = zf;
     const int grid = bricks_of(Lf) * nrhs;
     if (grid == 0) return;
-    const bool hc = Lf.hcoarse;
-#define DG_P(NF, NC, HC)                                                                                \
-    if (Lf.n == NF && Lc.n == NC && hc == HC) {                                                        \
-        constexpr int BE = be_of<NF>();                                                                \
-        constexpr int WG = wg_of(NF * BE * NF * BE);                                                   \
-        hipLaunchKernelGGL((k_prolong<T, NF, BE, NC, HC>), dim3(grid), dim3(WG), 0, s, a);             \
-        return;                                                                                        \
-    }
-    DG_TRANSFER_CASES(DG_P)
-#undef DG_P
-    fprintf(stderr, "dg: no prolongation kernel for %d -> %d\n", Lf.n, Lc.n);
+    constexpr int BE = be_of<2>();
+    hipLaunchKernelGGL((k_prolong<T, 2, BE, 2, true>), dim3(grid), dim3(wg_of(2 * BE * 2 * BE)), 0, s, a);
 }
 
 template void launch_restrict<double>(const LevelHost&, const LevelDev<double>*, const LevelHost&,
@@ -2509,7 +2647,13 @@ __global__ __launch_bounds__(256) void k_finalize(int what, RhsState* st, const 
     if (gated && !S.active) return;
     double acc = 0.0;
     const double* p = partial + (long long)rhs * pstride;
-    for (int i = threadIdx.x; i < nblk; i += 256) acc += p[i];
+    for (int i = threadIdx.x; i < nblk; i += 1024) {  // four loads in flight, added in order
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = p[min(i + q * 256, nblk - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc += i + q * 256 < nblk ? v[q] : 0.0;
+    }
     red[threadIdx.x] = acc;
     __syncthreads();
     for (int off = 128; off > 0; off >>= 1) {

@@ -275,23 +275,29 @@ void build_axis(int E, int p, double lo, double hi, double eps, AxisDev<double>&
 // Interior block in reference units (J = 1): stiffness D^T diag(w) D plus the
 // own-element halves of both interior faces; the penalty sigma J =
 // (p+1)^2 / (2 eps) follows from sigma = (p+1)^2 / (eps h) with h = 2J.
-void build_ref(int p, double eps, const double h[3], RefDev<double>& r) {
+void build_ref(int p, double eps, const double h[3], RefDev<double>& r, int family) {
     const int n = p + 1;
-    std::vector<double> xi, w, D;
-    gll(p, xi, w, D);
+    std::vector<double> xi, w, D, Le, Ge;
+    node_rule(p, family, xi, w, D);
     std::memset(&r, 0, sizeof(r));
     const double sig = (p + 1.0) * (p + 1.0) / (2.0 * eps);
     r.sig = sig;
+    if (family == 1) {
+        const std::vector<double> ends = {-1.0, 1.0};
+        lagrange_eval(xi, ends, Le);
+        lagrange_deriv(xi, ends, Ge);
+    }
     for (int l = 0; l < n; ++l) {
-        r.aL[l] = D[0 * n + l];
-        r.aR[l] = D[p * n + l];
+        r.aL[l] = family == 1 ? Ge[l] : D[0 * n + l];
+        r.aR[l] = family == 1 ? Ge[n + l] : D[p * n + l];
+        r.eL[l] = family == 1 ? Le[l] : (l == 0);
         r.w[l] = w[l];
     }
     for (int i = 0; i < n; ++i)
         for (int j = 0; j < n; ++j) {
             double v = 0.0;
             for (int q = 0; q < n; ++q) v += D[q * n + i] * w[q] * D[q * n + j];
-            const double eLi = (i == 0), eLj = (j == 0), eRi = (i == p), eRj = (j == p);
+            const double eLi = r.eL[i], eLj = r.eL[j], eRi = r.eL[p - i], eRj = r.eL[p - j];
             v += 0.5 * (eLi * r.aL[j] + r.aL[i] * eLj) + sig * eLi * eLj;
             v += -0.5 * (eRi * r.aR[j] + r.aR[i] * eRj) + sig * eRi * eRj;
             r.B[i][j] = v;
