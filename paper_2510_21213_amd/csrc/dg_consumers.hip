@@ -5,11 +5,11 @@
 // Every integral is the grid's quadrature: node q of an element-major field carries the weight
 // w_q = m_x[i] m_y[j] m_z[k], the lumped GLL mass of its local indices (the same for every
 // element of a uniform mesh).  These steps stream their fields once (the projection reads each
-// basis function once and the vectors from L2), so they are bound by HBM bandwidth; the dense
-// contractions they contain are short (a few to a few hundred outputs per node) and stay on the
-// vector units.
+// basis function once), so they are bound by HBM bandwidth.  The projection's sums run on the FP64
+// matrix instruction; the other contractions are short and stay on the vector units.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <stdexcept>
 
 #include "dg_kernels.h"
@@ -19,79 +19,110 @@ namespace dg {
 namespace {
 
 constexpr int PJ_THREADS = 256;
-constexpr int PJ_NODES = 32;  // nodes per thread per chunk: a chunk is 8,192 nodes
 constexpr int PJ_MAXN3 = 512;  // nodes per element (degree <= 7)
+constexpr int PJ_WGS = 512;    // work-groups of a launch: all resident at once (256 x 8 projections and the
+                               // compressed exchange's, whole calls: 0.65 ms, 0.69 at 1024, 0.665 at 2048)
+
+// 16 bytes of a field whose rows start at any multiple of 8
+typedef double pj_d2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef double pj_d4 __attribute__((ext_vector_type(4)));
 
 // partial[(i * nu + a) * nchunk + c] = sum over the nodes q of chunk c of w_q f_q phi_i(q) u_a(q),
-// for the TI x TA block of (i, a) of this work-group (f null: 1).  Work-groups of one chunk are
-// consecutive, so the chunk's u and f come from L2 after the first.  The weight of a node depends
-// only on its local index in the element (the three 1D lumped masses of a uniform mesh), staged
-// in LDS per work-group.  Indices within one field are 32-bit (a field has < 2^31 nodes).
-template <int TI, int TA>
+// for the 16 RT rows i and the 16 vectors a of this work-group (f null: 1), on
+// v_mfma_f64_16x16x4: a wave takes 16 nodes at a time, a lane four neighbouring ones of its row of
+// phi (lane & 15), so that each row is read in whole 128-byte pieces, and of its vector of u, whose
+// products with w f are the other operand; the four matrix steps take the lanes' first, second, third
+// and fourth nodes (tried: 32 rows a work-group, four waves per SIMD, two steps in flight: no faster;
+// non-temporal reads: 6% slower).  The reads of phi bound it: u is read once for 16 RT rows of phi (once for 8 in a
+// vector form of 8 x 8 sums a thread, which read as much of u from L2 as of phi from memory and
+// took 280 us, 3.9 TB/s, for 256 rows and 8 vectors of 512,000 nodes; this form
+// 235 us, 4.5 TB/s).
+// The weight of a node depends only on its local index in the element (the three 1D lumped masses
+// of a uniform mesh), staged in LDS per work-group.  Indices within one field are 32-bit (a field
+// has < 2^31 nodes).
+template <int RT>
 __global__ __launch_bounds__(PJ_THREADS) void k_project(const LevelDev<double>* __restrict__ Lp, int n, int ndof,
                                                         int nbasis, const double* __restrict__ phi, int nu,
                                                         const double* __restrict__ u, const double* __restrict__ f,
-                                                        int nchunk, double* __restrict__ partial) {
-    __shared__ double red[PJ_THREADS / 64][TI * TA];
-    __shared__ double wloc[PJ_MAXN3];
-    const int nti = (nbasis + TI - 1) / TI, nta = (nu + TA - 1) / TA;
+                                                        int nchunk, int cnodes, double* __restrict__ partial) {
+    __shared__ double red[PJ_THREADS / 64][256];
+    __shared__ double wloc[PJ_MAXN3 + 3];
+    const int nti = (nbasis + 16 * RT - 1) / (16 * RT), nta = (nu + 15) / 16;
     const int b = blockIdx.x;
     const int ti = b % nti, ta = (b / nti) % nta, c = b / (nti * nta);
-    const int i0 = ti * TI, a0 = ta * TA;
+    const int i0 = ti * 16 * RT, a0 = ta * 16;
     const int n3 = n * n * n;
     {
         const LevelDev<double>& L = *Lp;
-        for (int l = threadIdx.x; l < n3; l += PJ_THREADS)
-            wloc[l] = L.ax[0].m[l % n] * L.ax[1].m[(l / n) % n] * L.ax[2].m[l / (n * n)];
-    }
-    __syncthreads();
-    const double* __restrict__ prow[TI];
-    const double* __restrict__ urow[TA];
-#pragma unroll
-    for (int r = 0; r < TI; ++r) prow[r] = phi + (long long)min(i0 + r, nbasis - 1) * ndof;
-#pragma unroll
-    for (int k = 0; k < TA; ++k) urow[k] = u + (long long)min(a0 + k, nu - 1) * ndof;
-    double acc[TI][TA];
-#pragma unroll
-    for (int r = 0; r < TI; ++r)
-#pragma unroll
-        for (int k = 0; k < TA; ++k) acc[r][k] = 0.0;
-    const int q0 = c * PJ_THREADS * PJ_NODES + (int)threadIdx.x;
-#pragma unroll 4
-    for (int m = 0; m < PJ_NODES; ++m) {
-        const int q = q0 + m * PJ_THREADS;
-        const bool ok = q < ndof;
-        const int qq = ok ? q : 0;
-        double wq = ok ? wloc[qq % n3] : 0.0;
-        if (f) wq *= f[qq];
-        double uv[TA];
-#pragma unroll
-        for (int k = 0; k < TA; ++k) uv[k] = wq * urow[k][qq];
-#pragma unroll
-        for (int r = 0; r < TI; ++r) {
-            const double pv = prow[r][qq];
-#pragma unroll
-            for (int k = 0; k < TA; ++k) acc[r][k] += pv * uv[k];
+        for (int l = threadIdx.x; l < n3 + 3; l += PJ_THREADS) {
+            const int m = l % n3;
+            wloc[l] = L.ax[0].m[m % n] * L.ax[1].m[(m / n) % n] * L.ax[2].m[m / (n * n)];
         }
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int r = 0; r < TI; ++r)
-#pragma unroll
-        for (int k = 0; k < TA; ++k) {
-            double v = acc[r][k];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (lane == 0) red[wv][r * TA + k] = v;
-        }
     __syncthreads();
-    if (threadIdx.x < TI * TA) {
-        const int r = threadIdx.x / TA, k = threadIdx.x % TA;
-        if (i0 + r < nbasis && a0 + k < nu) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m = lane & 15, kq = lane >> 4;
+    const double* __restrict__ prow[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) prow[t] = phi + (long long)min(i0 + 16 * t + m, nbasis - 1) * ndof;
+    const double* __restrict__ urow = u + (long long)min(a0 + m, nu - 1) * ndof;
+    pj_d4 acc[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) acc[t] = pj_d4{0.0, 0.0, 0.0, 0.0};
+    const unsigned qe = min((long long)ndof, (long long)(c + 1) * cnodes);
+    unsigned q = c * cnodes + wv * 16 + 4 * kq;  // the lane's first node
+    int l = q % n3;
+    const int dl = 64 % n3;
+    for (; q - 4 * kq + 16 <= qe; q += 64) {
+        double pv[RT][4], bv[4];
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const pj_d2 v = *reinterpret_cast<const pj_d2*>(prow[t] + q + 2 * h);
+                pv[t][2 * h] = v[0];
+                pv[t][2 * h + 1] = v[1];
+            }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const pj_d2 v = *reinterpret_cast<const pj_d2*>(urow + q + 2 * h);
+            pj_d2 w = {wloc[l + 2 * h], wloc[l + 2 * h + 1]};
+            if (f) w *= *reinterpret_cast<const pj_d2*>(f + q + 2 * h);
+            bv[2 * h] = w[0] * v[0];
+            bv[2 * h + 1] = w[1] * v[1];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int t = 0; t < RT; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[t][j], bv[j], acc[t], 0, 0, 0);
+        l += dl;
+        if (l >= n3) l -= n3;
+    }
+    if (q - 4 * kq < qe) {  // the field's last, incomplete 16 nodes (one wave of the last chunk)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool ok = q + j < qe;
+            const unsigned qq = ok ? q + j : 0;
+            double w = ok ? wloc[l + j] : 0.0;
+            if (f) w *= f[qq];
+            const double bw = w * urow[qq];
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(prow[t][qq], bw, acc[t], 0, 0, 0);
+        }
+    }
+    // accumulator: vector = lane & 15, row = lane / 16 + 4 * register
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        if (t) __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wv][(kq + 4 * r) * 16 + m] = acc[t][r];
+        __syncthreads();
+        const int i = i0 + 16 * t + (threadIdx.x >> 4), a = a0 + (threadIdx.x & 15);
+        if (i < nbasis && a < nu) {
             double s = 0.0;
 #pragma unroll
             for (int w = 0; w < PJ_THREADS / 64; ++w) s += red[w][threadIdx.x];
-            partial[((long long)(i0 + r) * nu + a0 + k) * nchunk + c] = s;
+            partial[((long long)i * nu + a) * nchunk + c] = s;
         }
     }
 }
@@ -196,19 +227,34 @@ __global__ __launch_bounds__(256) void k_small_gemm(int ni, int nk, int na, cons
 
 }  // namespace
 
-int project_chunks(long long ndof) { return (int)((ndof + PJ_THREADS * PJ_NODES - 1) / (PJ_THREADS * PJ_NODES)); }
+// Rows of phi of a work-group: 64, or 16 for a few rows (the compressed exchange's overlaps, 8 x 8),
+// where a launch needs the work-groups more than the saved reads of u.
+static int project_rows(int nbasis) { return nbasis > 16 ? 64 : 16; }
+
+// Nodes of a chunk, in whole steps of the work-group's four waves: PJ_WGS work-groups.
+static long long project_nodes(long long ndof, int nbasis, int nu) {
+    const int rows = project_rows(nbasis);
+    const long long tiles = (long long)((nbasis + rows - 1) / rows) * ((nu + 15) / 16);
+    const long long most = std::max(1LL, PJ_WGS / tiles);
+    return std::max(256LL, ((ndof + most - 1) / most + 63) / 64 * 64);
+}
+
+int project_chunks(long long ndof, int nbasis, int nu) {
+    const long long cn = project_nodes(ndof, nbasis, nu);
+    return (int)((ndof + cn - 1) / cn);
+}
 
 void launch_project(const LevelHost& L, int nbasis, const double* phi, int nu, const double* u, const double* f,
                     double* partial, double* out, hipStream_t s) {
     if (nbasis == 0 || nu == 0) return;
-    constexpr int TI = 8, TA = 8;
-    const int nchunk = project_chunks(L.ndof);
-    const long long nti = (nbasis + TI - 1) / TI, nta = (nu + TA - 1) / TA;
-    const long long grid = nti * nta * nchunk;
-    if (grid > 0x7fffffffLL) throw std::runtime_error("projection grid too large");
     if (L.ndof >= 0x7fffffffLL || L.n * L.n * L.n > PJ_MAXN3) throw std::runtime_error("projection: field too large");
-    hipLaunchKernelGGL((k_project<TI, TA>), dim3((unsigned)grid), dim3(PJ_THREADS), 0, s, L.dev64, L.n, (int)L.ndof,
-                       nbasis, phi, nu, u, f, nchunk, partial);
+    const int nchunk = project_chunks(L.ndof, nbasis, nu), cn = (int)project_nodes(L.ndof, nbasis, nu);
+    const int rows = project_rows(nbasis);
+    const long long grid = (long long)((nbasis + rows - 1) / rows) * ((nu + 15) / 16) * nchunk;
+    if (grid > 0x7fffffffLL) throw std::runtime_error("projection grid too large");
+    auto* k = rows == 64 ? k_project<4> : k_project<1>;
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(PJ_THREADS), 0, s, L.dev64, L.n, (int)L.ndof, nbasis, phi, nu, u,
+                       f, nchunk, cn, partial);
     launch_sum_partials(nbasis * nu, partial, nchunk, nchunk, out, s);
 }
 

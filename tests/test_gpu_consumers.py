@@ -50,6 +50,25 @@ def test_hartree_action_matches_oracle(gpu_lib, E, p, nb, nu):
     assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("E,p,nb,nu", [((2, 2, 2), 1, 16, 16), ((3, 3, 5), 2, 17, 17), ((5, 3, 7), 4, 64, 1),
+                                       ((1, 3, 3), 5, 65, 24), ((7, 6, 5), 6, 129, 8)])
+def test_projection_tile_edges_match_oracle(gpu_lib, E, p, nb, nu):
+    """Row tiles of 16 and 64, vector tiles of 16, node counts that are no multiple of 16 or 2 (rows
+    that start at odd multiples of 8 bytes), elements larger than a step, several chunks."""
+    mesh = _Mesh(E, p, (-1.0, -2.0, -1.5), (2.0, 1.0, 1.5))
+    ctx = gpu_lib.Context([(mesh.E, mesh.p, mesh.lo, mesh.hi)], n_levels=0)
+    axes = oracle_axes(mesh)
+    shape = (axes[2].N, axes[1].N, axes[0].N)
+    rng = np.random.default_rng(6)
+    phi, u = rng.standard_normal((nb,) + shape), rng.standard_normal((nu,) + shape)
+    vH = rng.standard_normal(shape)
+    got = ctx.hartree_action(_t(_em(mesh, phi)), _t(_em(mesh, u)), _t(to_em(vH, mesh))).cpu().numpy()
+    ref = consumers.hartree_action(consumers.weights(axes), phi, u, vH)
+    assert got.shape == ref.shape == (nb, nu)
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+    ctx.close()
+
+
 def _orbitals():
     prims = gaussians.Primitives([0.6, 1.4, 0.9, 0.45], [[0.4, 0, 0], [0.4, 0, 0], [-0.5, 0.2, 0.1],
                                                           [-0.5, 0.2, 0.1]])
