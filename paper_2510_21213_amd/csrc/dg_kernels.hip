@@ -710,6 +710,42 @@ __device__ __forceinline__ void pair_row(const SlabCoef<T, N, GL>& c, const T* s
     }
 }
 
+// LDS strides of the slab kernels, in values: rows and planes of the staged layer, rows and planes of its
+// x (and y) terms.  The lanes of a wave write a layer by nodes (i, j) of elements and read it by rows,
+// RS apart, or columns; with the strides left at the widths of the rows the accesses of a p = 4 layer took
+// 3.7 times the cycles they need (SQ_LDS_BANK_CONFLICT; the LDS was busy 45% of the FP32 smoothing
+// step's time).  The paddings are the least-conflict ones of a count over all accesses of a layer, 32
+// banks of 4 bytes, within the LDS that the registers' occupancy leaves.   Step of 128 right-hand sides of
+// 32^3 elements, BF16 fields: conflict cycles 497 -> 210 a wave, 1473 -> 1449 us; whole solves 1 to 3%.
+// PLAIN: no padding (the restriction steps of degree 4, whose third array would cost them a work-group
+// per CU: 1.51 ms against 1.44).
+template <typename T, int N, int TX, int TY, bool PLAIN = false>
+struct SlabLds {
+    static constexpr bool D = sizeof(T) == 8;
+    static constexpr int NX = TX * N, NY = TY * N;
+    static constexpr int rs(int wide) {
+        if (PLAIN) return wide;
+        if (N == 2) return wide + 1;                             // 21
+        if (N == 3) return D ? wide + 3 : wide + 7;              // 21, 25
+        if (N == 4) return TY == 4 ? wide + 3 : D ? wide + 4 : wide;
+        if (N == 5) return TX == 2 ? wide + 1 : TY == 2 ? wide + 9 : wide + 7;
+        if (N == 6) return D ? wide + 1 : wide + 5;
+        return wide + (N == 7 ? 9 : 0);
+    }
+    static constexpr int pad() {
+        if (PLAIN) return 0;
+        if (N == 2) return D ? 0 : 12;
+        if (N == 3) return D ? 2 : 10;
+        if (N == 4) return TY == 4 ? 8 : 2;
+        if (N == 5) return TX == 2 ? (D ? 6 : 14) : TY == 2 ? 8 : 14;
+        return N == 6 ? 4 : 2;
+    }
+    static constexpr int RS = rs(NX + 2 * N), PS = RS * (NY + 2 * N) + pad();
+    static constexpr bool W = N == 5 && TX == 4 && TY == 2;
+    static constexpr int OR = PLAIN ? NX : W || (N == 4 && D) ? NX + 3 : NX + 1;
+    static constexpr int OP = OR * NY + (W && !PLAIN ? 14 : 0);
+};
+
 typedef __amdgpu_buffer_rsrc_t brsrc;
 
 // Raw buffer access (byte offsets; voff per lane, soff uniform).  Loads outside
@@ -850,7 +886,8 @@ template <int N, int TX, int TY>
 __device__ __forceinline__ void mf_ghosts(const SlabCoef<float, N>& c, float* su, int tx0, int ty0, int E0,
                                           int E1) {
 #pragma clang fp contract(off)
-    constexpr int NX = TX * N, NY = TY * N, RS = NX + 2 * N, PS = RS * (NY + 2 * N);
+    constexpr int NX = TX * N, NY = TY * N, RS = SlabLds<float, N, TX, TY>::RS,
+                  PS = SlabLds<float, N, TX, TY>::PS;
     const int nvx = min(TX, E0 - tx0), nvy = min(TY, E1 - ty0);  // valid elements of the tile per axis
     const bool lx = tx0 == 0, rx = tx0 + TX >= E0, ly = ty0 == 0, ry = ty0 + TY >= E1;
     const int t = threadIdx.x;
@@ -900,7 +937,8 @@ __device__ __forceinline__ void mf_ghosts(const SlabCoef<float, N>& c, float* su
 // matrix cores.  Lines of elements outside the mesh produce values nobody reads.
 template <int N, int TX, int TY>
 __device__ __forceinline__ void mf_xy_terms(const RefDev<float>& R, const mf_s4& Aop, const float* su, float* sxy) {
-    constexpr int NX = TX * N, NY = TY * N, RS = NX + 2 * N, PS = RS * (NY + 2 * N), OR = NX, OP = OR * NY;
+    constexpr int NX = TX * N, NY = TY * N, RS = SlabLds<float, N, TX, TY>::RS, PS = SlabLds<float, N, TX, TY>::PS,
+                  OR = SlabLds<float, N, TX, TY>::OR, OP = SlabLds<float, N, TX, TY>::OP;
     constexpr int NLX = NY * N * TX, NLY = NX * N * TY;       // element lines per axis in the layer
     constexpr int NBX = (NLX + 15) / 16, NBY = (NLY + 15) / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
@@ -969,8 +1007,8 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N), (slab_waves<T, N, TX, TY, MODE
 #pragma clang fp contract(off)
     constexpr int NX = TX * N, NY = TY * N, NT = NX * NY, N2 = N * N, N3 = N2 * N;
     constexpr int WG = wg_of(NT);
-    constexpr int RS = NX + 2 * N, PS = RS * (NY + 2 * N);  // LDS staging: row and plane strides
-    constexpr int OR = NX, OP = OR * NY;                     // LDS x / y terms: row and plane strides
+    using Lds = SlabLds<T, N, TX, TY, MODE == BM_RESTRICT && N == 5>;
+    constexpr int RS = Lds::RS, PS = Lds::PS, OR = Lds::OR, OP = Lds::OP;
     constexpr int NP = NT / 2;                               // element pairs per axis and layer
     // first thread of the y pairs: the next wave boundary when the work-group still holds all
     // y pairs from there, so that no wave computes both an x and a y pair row
@@ -1102,14 +1140,14 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N), (slab_waves<T, N, TX, TY, MODE
     bool pok;
     T psc;
     if (isx) {
-        const int pa = t % (TX / 2), row = t / (TX / 2), Yr = row % NY, kr = row / NY;
+        const int row = t % (NY * N), pa = t / (NY * N), Yr = row % NY, kr = row / NY;
         pe = tx0 + 2 * pa;
         pok = pe < E0 && ty0 + Yr / N < E1;
         pb = kr * PS + (Yr + N) * RS + 2 * pa * N;
         ob = kr * OP + Yr * OR + 2 * pa * N;
         psc = R.scale[0] * R.w[Yr % N] * R.w[kr];
     } else {
-        const int q = min(max(t - YB, 0), NP - 1), pa = q % (TY / 2), col = q / (TY / 2), Xc = col % NX, kr = col / NX;
+        const int q = min(max(t - YB, 0), NP - 1), col = q % (NX * N), pa = q / (NX * N), Xc = col % NX, kr = col / NX;
         pe = ty0 + 2 * pa;
         pok = isy && pe < E1 && tx0 + Xc / N < E0;
         pb = kr * PS + 2 * pa * N * RS + Xc + N;
@@ -2333,6 +2371,9 @@ __global__ __launch_bounds__(256) void k_coarse_xy_fwd(const CoarseDev* __restri
     }
 }
 
+// A chain of loads in a few work-groups: all of a thread's entries of Q and of its line are read at
+// once (those past the level's nodes per axis are in the CMAX x CMAX arrays, or the line's last again, and
+// not used).
 __global__ __launch_bounds__(256) void k_coarse_z(const CoarseDev* __restrict__ Cp, long long ndof, const RhsState* st,
                                                   const double* __restrict__ g1, double* __restrict__ g2) {
     __shared__ double sv[16][CMAX + 1];
@@ -2342,19 +2383,27 @@ __global__ __launch_bounds__(256) void k_coarse_z(const CoarseDev* __restrict__ 
     const int nx = C.n[0], nxy = nx * C.n[1], nz = C.n[2];
     const int ln = t / 16, k = t % 16, line = blockIdx.x * 16 + ln;  // 16 z lines of 16 entries
     const bool ok = line < nxy && k < nz;
-    const double* a1 = g1 + (long long)rhs * ndof;
+    const int lc = min(line, nxy - 1);
+    const double* a1 = g1 + (long long)rhs * ndof + lc;
+    double qf[CMAX], qb[CMAX], av[CMAX];
+#pragma unroll
+    for (int c = 0; c < CMAX; ++c) {
+        qf[c] = C.Q[2][c][k];
+        qb[c] = C.Q[2][k][c];
+        av[c] = a1[(long long)min(c, nz - 1) * nxy];
+    }
+    const double lam = C.lam[0][lc % nx] + C.lam[1][lc / nx] + C.lam[2][k];
     double v = 0.0;
-    if (ok) {
-        for (int Z = 0; Z < nz; ++Z) v += C.Q[2][Z][k] * a1[(long long)Z * nxy + line];
-        v /= (C.lam[0][line % nx] + C.lam[1][line / nx] + C.lam[2][k]);
-    }
-    sv[ln][k] = v;
+#pragma unroll
+    for (int Z = 0; Z < CMAX; ++Z)
+        if (Z < nz) v += qf[Z] * av[Z];
+    sv[ln][k] = ok ? v / lam : 0.0;
     __syncthreads();
-    if (ok) {
-        double w = 0.0;
-        for (int c = 0; c < nz; ++c) w += C.Q[2][k][c] * sv[ln][c];
-        g2[(long long)rhs * ndof + (long long)k * nxy + line] = w;
-    }
+    double w = 0.0;
+#pragma unroll
+    for (int c = 0; c < CMAX; ++c)
+        if (c < nz) w += qb[c] * sv[ln][c];
+    if (ok) g2[(long long)rhs * ndof + (long long)k * nxy + line] = w;
 }
 
 template <typename T>
@@ -2493,16 +2542,22 @@ __global__ __launch_bounds__(256) void k_update(const T* __restrict__ dinv, long
     const long long base = (long long)rhs * ndof;
     const long long q0 = (long long)blockIdx.y * 1024 + threadIdx.x;
     double acc = 0.0;
+    T xv[4], pv[4], rv[4], qv[4], dv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {  // all loads in flight at once: past the end, the last value again
+        const long long q = min(q0 + v * 256, ndof - 1), g = base + q;
+        xv[v] = x[g], pv[v] = p[g], rv[v] = r[g], qv[v] = q_[g], dv[v] = dinv[q];
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const long long q = q0 + v * 256;
         if (q < ndof) {
             const long long g = base + q;
-            x[g] += alpha * p[g];
-            const T rn = r[g] - alpha * q_[g];
+            x[g] = xv[v] + alpha * pv[v];
+            const T rn = rv[v] - alpha * qv[v];
             r[g] = rn;
             acc += (double)rn * (double)rn;
-            if (z1) z1[g] = c0 * rn * dinv[q];
+            if (z1) z1[g] = c0 * rn * dv[v];
         }
     }
     const double s = block_sum<256>(acc, red);
@@ -2534,22 +2589,28 @@ __global__ __launch_bounds__(256) void k_update_pc(const double* __restrict__ di
     const double alpha = st[rhs].alpha;
     const long long base = (long long)rhs * ndof;
     const long long q0 = (long long)blockIdx.y * 1024 + threadIdx.x;
-    double acc = 0.0;
+    double acc = 0.0, xv[4], rv[4], qv[4], dv[4];
+    TP pv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {  // all loads in flight at once: past the end, the last value again
+        const long long q = min(q0 + v * 256, ndof - 1), g = base + q;
+        xv[v] = x[g], pv[v] = p[g], rv[v] = r[g], qv[v] = q_[g], dv[v] = dinv[q];
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const long long q = q0 + v * 256;
         if (q < ndof) {
             const long long g = base + q;
-            x[g] += alpha * (double)p[g];
-            const double rn = r[g] - alpha * q_[g];
+            x[g] = xv[v] + alpha * (double)pv[v];
+            const double rn = rv[v] - alpha * qv[v];
             r[g] = rn;
             acc += rn * rn;
             if constexpr (std::is_same<TO, __bf16>::value) {
                 r32[g] = to_bf16((float)rn);
-                z1[g] = to_bf16((float)(c0 * rn * dinv[q]));
+                z1[g] = to_bf16((float)(c0 * rn * dv[v]));
             } else {
                 r32[g] = (float)rn;
-                z1[g] = (float)(c0 * rn * dinv[q]);
+                z1[g] = (float)(c0 * rn * dv[v]);
             }
         }
     }
@@ -2565,17 +2626,22 @@ __global__ __launch_bounds__(256) void k_to32_cheb0(const double* __restrict__ d
     if (st && !st[rhs].active) return;
     const long long base = (long long)rhs * ndof;
     const long long q0 = (long long)blockIdx.y * 1024 + threadIdx.x;
+    double rv[4], dv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const long long q = min(q0 + v * 256, ndof - 1);
+        rv[v] = r[base + q], dv[v] = dinv[q];
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const long long q = q0 + v * 256;
         if (q < ndof) {
-            const double rv = r[base + q];
             if constexpr (std::is_same<TO, __bf16>::value) {
-                r32[base + q] = to_bf16((float)rv);
-                z1[base + q] = to_bf16((float)(c0 * rv * dinv[q]));
+                r32[base + q] = to_bf16((float)rv[v]);
+                z1[base + q] = to_bf16((float)(c0 * rv[v] * dv[v]));
             } else {
-                r32[base + q] = (float)rv;
-                z1[base + q] = (float)(c0 * rv * dinv[q]);
+                r32[base + q] = (float)rv[v];
+                z1[base + q] = (float)(c0 * rv[v] * dv[v]);
             }
         }
     }
@@ -2616,11 +2682,16 @@ __global__ __launch_bounds__(256) void k_dot(long long ndof, const RhsState* st,
     const long long base = (long long)rhs * ndof;
     const long long q0 = (long long)blockIdx.x * 1024 + threadIdx.x;
     double acc = 0.0;
+    TA av[4];
+    TB bv[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const long long q = q0 + v * 256;
-        if (q < ndof) acc += (double)a[base + q] * (double)b[base + q];
+        const long long g = base + min(q0 + v * 256, ndof - 1);
+        av[v] = a[g], bv[v] = b[g];
     }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        if (q0 + v * 256 < ndof) acc += (double)av[v] * (double)bv[v];
     const double s = block_sum<256>(acc, red);
     if (threadIdx.x == 0) partial[(long long)rhs * pstride + blockIdx.x] = s;
 }
@@ -2644,7 +2715,7 @@ __global__ __launch_bounds__(256) void k_finalize(int what, RhsState* st, const 
     RhsState& S = st[rhs];
     const bool gated = (what == FIN_RZ || what == FIN_PQ || what == FIN_RR || what == FIN_FLEX || what == FIN_RZ0 ||
                         what == FIN_CR || what == FIN_CAC);
-    if (gated && !S.active) return;
+    const int act = S.active;  // the partial sums do not wait for it
     double acc = 0.0;
     const double* p = partial + (long long)rhs * pstride;
     for (int i = threadIdx.x; i < nblk; i += 1024) {  // four loads in flight, added in order
@@ -2654,14 +2725,15 @@ __global__ __launch_bounds__(256) void k_finalize(int what, RhsState* st, const 
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc += i + q * 256 < nblk ? v[q] : 0.0;
     }
+    if (gated && !act) return;
     red[threadIdx.x] = acc;
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
-    }
+    if (threadIdx.x >= 64) return;
+    // halves added pairwise: 256 -> 64 sums in LDS, the rest in the wave
+    double s = (red[threadIdx.x] + red[threadIdx.x + 128]) + (red[threadIdx.x + 64] + red[threadIdx.x + 192]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
     if (threadIdx.x != 0) return;
-    const double s = red[0];
     switch (what) {
         case FIN_BB: S.bb = s; break;
         case FIN_RR0:
