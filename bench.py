@@ -1081,7 +1081,9 @@ def main_quadrature(args):
         b.record()
     torch.cuda.synchronize()
     dt_g = float(np.mean([a.elapsed_time(b) for a, b in ev])) * 1e-3
-    flops = float(nface) * ndof * (9 + 2 * npairs)
+    # the sum runs over octants (the box's reflections): an eighth of the boundary nodes times an eighth
+    # of the grid nodes, per pair 8 image distances, their 8 parity combinations, 8 parities of a source
+    flops = float(nface) * ndof / 64 * (8 * 9 + 24 + 16 * npairs)
     achieved = flops / dt_g / 1e12
     g_h = g.cpu().numpy().reshape(npairs, nface)
     g_cf_h = g_cf.cpu().numpy().reshape(npairs, nface)
@@ -1110,10 +1112,10 @@ def main_quadrature(args):
                      "achieved": achieved, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_FP64_TFLOPS,
                      "traffic": measured_traffic("boundary_quadrature_exchange8.md", "dg_boundary.hip", "fp64"),
-                     "traffic_unit": "bytes per launch of k_quad (rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE x1.0)",
+                     "traffic_unit": "bytes per call of the k_quad kernels (rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE x1.0)",
                      "algorithmic_flops_per_launch": flops,
-                     "flop_count": "per boundary-node/grid-node pair 9 (distance 8, reciprocal root 1) "
-                                   "plus 2 per source",
+                     "flop_count": "per pair of octant nodes 8 image distances of 9 (distance 8, reciprocal root 1), "
+                                   "24 for their parity combinations and 16 per source",
                      "avg_launch_us": 1e6 * dt_g, "timing_source": "HIP events on the call's stream"},
         "cpu_baseline": cpu,
         "check_vs_oracle": check,
