@@ -715,7 +715,7 @@ __device__ __forceinline__ void pair_row(const SlabCoef<T, N, GL>& c, const T* s
 // RS apart, or columns; with the strides left at the widths of the rows the accesses of a p = 4 layer took
 // 3.7 times the cycles they need (SQ_LDS_BANK_CONFLICT; the LDS was busy 45% of the FP32 smoothing
 // step's time).  The paddings are the least-conflict ones of a count over all accesses of a layer, 32
-// banks of 4 bytes, within the LDS that the registers' occupancy leaves.   Step of 128 right-hand sides of
+// banks of 4 bytes, within the LDS that the registers' occupancy leaves.  Step of 128 right-hand sides of
 // 32^3 elements, BF16 fields: conflict cycles 497 -> 210 a wave, 1473 -> 1449 us; whole solves 1 to 3%.
 // PLAIN: no padding (the restriction steps of degree 4, whose third array would cost them a work-group
 // per CU: 1.51 ms against 1.44).
@@ -989,9 +989,11 @@ __device__ __forceinline__ void mf_xy_terms(const RefDev<float>& R, const mf_s4&
 
 // Waves per SIMD that the registers are held to where the compiler meets the count or misses it by a
 // few: six (80 VGPRs) for the FP32 smoothing steps of degree 4 on 4x2 tiles (at 81, five waves: 36
-// right-hand sides of 16^3 elements in BF16F_PC 17.6 ms, at 80 16.9), three (168) for the FP64 ones.
+// right-hand sides of 16^3 elements in BF16F_PC 17.6 ms, at 80 16.9), three (168) for the FP64 ones of
+// degrees 4 and 5.  Never below what a step needs: no slab kernel spills.
 template <typename T, int N, int TX, int TY, int MODE, bool MF, bool GL>
 constexpr int slab_waves() {
+    if (sizeof(T) == 8 && N == 6 && MODE == BM_CHEB && !GL) return 3;
     if (N != 5 || TY != 2 || MF || GL) return 1;
     if (sizeof(T) == 4) return TX == 4 && MODE == BM_CHEB ? 6 : 1;
     return TX == 2 && (MODE == BM_CHEB || MODE == BM_CHEBDOT) ? 3 : 1;
@@ -1168,10 +1170,11 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N), (slab_waves<T, N, TX, TY, MODE
     for (int s = 0; s < HS; ++s) load_col<T, N, MODE, S, ZP, SP>(hal[s], ru, ru2, hoff[s], (uint32_t)ezb * lstride, beta);
     if (ezb + 1 < E2) load_col<T, N, MODE, S, ZP, SP>(nxt, ru, ru2, coff, (uint32_t)(ezb + 1) * lstride, beta);
     // cr / D for the nodes of an interior layer, and for the bottom / top node of a boundary layer
-    T crD[N], crD0 = 0, crDN = 0;
+    constexpr int NM = (N + 1) / 2;  // w_k and B_kk are those of the mirrored node
+    T crD[NM], crD0 = 0, crDN = 0;
     if constexpr (IS_CHEB) {
 #pragma unroll
-        for (int k = 0; k < N; ++k) crD[k] = a.cr * recip(fm(P1, R.w[k], P2 * R.B[k][k]));
+        for (int k = 0; k < NM; ++k) crD[k] = a.cr * recip(fm(P1, R.w[k], P2 * R.B[k][k]));
         crD0 = a.cr * recip(fm(P1, R.w[0], P2 * (R.B[0][0] + R.aL[0])));
         crDN = a.cr * recip(fm(P1, R.w[N - 1], P2 * (R.B[N - 1][N - 1] - R.aR[N - 1])));
     }
@@ -1271,7 +1274,7 @@ __global__ __launch_bounds__(wg_of(TX* TY* N* N), (slab_waves<T, N, TX, TY, MODE
                     fstore<S>(r, ro, coff, so);
                     if constexpr (MODE == BM_RESIDDOT) dots[zq] = fm((double)r, (double)r, dots[zq]);
                 } else if constexpr (IS_CHEB) {
-                    T cd = crD[k];
+                    T cd = crD[k < NM ? k : N - 1 - k];
                     if constexpr (GL) {
                         if (ez == 0 || ez == E2 - 1) {
                             T bd = R.B[k][k];

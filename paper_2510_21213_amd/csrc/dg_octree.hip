@@ -112,14 +112,14 @@ constexpr int OP_WGS = 4096;
 // link) and vector issue, about 40 % each of an FP32 wave's time at N = 5.  So the chain is walked once for a
 // chunk, and the next right-hand sides' nodes, neighbour lines and hanging neighbours' lines are asked for
 // while the present ones are computed.  Four waves a work-group: with five (a thread per line and right-hand
-// side) only one fitted a CU.  Registers: three waves per SIMD in FP32 at N = 5, two in FP64.
+// side) only one fitted a CU.  Registers: three waves per SIMD in FP32 from N = 4, two in FP64.
 // Measured (2,836 elements, N = 5, 36 right-hand sides; before: a thread per node, the pieces N at a time with
 // up to seven barriers a pass): FP32 product 238 -> 165 us, FP64 346 -> 276 us; level of degree 2 (FP32)
 // 83 -> 41 us; without hanging faces 76 us per as many elements.  The whole FP32-V-cycle solve 266 -> 174 ms.
 // Tried: neighbour elements staged whole in LDS axis by axis (194 us), four right-hand sides a thread without
 // the prefetch (205 us), a hanging face per lane group instead of a piece (207 us).
 template <int N, int MODE, int RB, typename T>
-__global__ __launch_bounds__(OT, sizeof(T) == 4 ? (N == 5 ? 3 : 4) : 2) void k_oct_op(OpRef<N, T> R, int ne, int nrhs, int chunk, const T* __restrict__ geo,
+__global__ __launch_bounds__(OT, sizeof(T) == 4 ? (N >= 4 ? 3 : 4) : 2) void k_oct_op(OpRef<N, T> R, int ne, int nrhs, int chunk, const T* __restrict__ geo,
                                               const Face* __restrict__ faces, const int* __restrict__ hstart,
                                               const Piece* __restrict__ pcs, const T* __restrict__ tab,
                                               const RhsState* __restrict__ st, const T* u, const T* uprev, const T* __restrict__ f, T* out,
