@@ -401,19 +401,25 @@ __global__ __launch_bounds__(QUAD_BLOCK, 2) void k_quad_mfma(const double* __res
 }
 
 // g at the eight images of an octant boundary node from its parity sums (S parts, face vectors `stride`
-// sources apart; part and g may be the same vectors).  A source with a value that is not finite has parity
-// sums that are not finite either; its data are then formed from its non-finite terms alone, as the plain
-// sum over all nodes would have them (an infinite value stays one, rather than infinity minus infinity).
-__global__ __launch_bounds__(256) void k_quad_combine(const double* part, int S, int R, QuadDims D, int nface,
-                                                      int nr, int r0, const LevelDev<double>* __restrict__ dev,
-                                                      int n, long long ndof, const double* __restrict__ xs,
-                                                      const double* __restrict__ ys, const double* __restrict__ zs,
-                                                      double drop2, const double* __restrict__ f,
-                                                      const double* __restrict__ phi, const int* __restrict__ pi,
-                                                      const int* __restrict__ pj, double* g) {
-    const long long t = blockIdx.x * 256LL + threadIdx.x;
-    if (t >= (long long)nr * D.nbo) return;
-    const int r = (int)(t / D.nbo), b = (int)(t % D.nbo);
+// sources apart; part and g may be the same vectors).  Grid (octant boundary nodes / 256, sources).
+//
+// A source with a value that is not finite has parity sums that are not finite either; its data are then
+// what the plain sum over all nodes gives (an infinite value stays one, rather than infinity minus infinity
+// between mirror images).  Every inverse distance is positive but the dropped one of the boundary node itself,
+// so that sum is infinite where the infinite terms have one sign, and NaN where they have two, where a term is
+// NaN or where the node's own term is infinite (0 times infinity).  The work-group looks through the source's
+// values together: 0.5 to 1.4 ms more for 512,000 nodes (a lane that walked the grid by itself would take a
+// dependent step a node).
+__global__ __launch_bounds__(256) void k_quad_combine(const double* part, int S, int R, QuadDims D, int nface, int r0,
+                                                      const LevelDev<double>* __restrict__ dev, int n, long long ndof,
+                                                      const double* __restrict__ xs, const double* __restrict__ ys,
+                                                      const double* __restrict__ zs, double drop2,
+                                                      const double* __restrict__ f, const double* __restrict__ phi,
+                                                      const int* __restrict__ pi, const int* __restrict__ pj,
+                                                      double* g) {
+    constexpr int POS = 1, NEG = 2, NAN_ = 4;
+    __shared__ int terms;
+    const int r = blockIdx.y, src = r0 + r, own = blockIdx.x * 256 + threadIdx.x, b = min(own, D.nbo - 1);
     int fc, X, Y, Z;
     oct_face_node(b, D, fc, X, Y, Z);
     const int self = self_mask(X, Y, Z, D);
@@ -429,27 +435,42 @@ __global__ __launch_bounds__(256) void k_quad_combine(const double* part, int S,
         finite &= isfinite(a);
     }
     parities(v);
-    if (!finite) {
-        double bad[8] = {};
-        bool any = false;
-        for (int zq = 0; zq < D.N[2]; ++zq)
-            for (int yq = 0; yq < D.N[1]; ++yq)
-                for (int xq = 0; xq < D.N[0]; ++xq) {
-                    const double a = quad_source(r0 + r, xq, yq, zq, D, n, ndof, dev, f, phi, pi, pj);
-                    if (isfinite(a)) continue;
-                    any = true;
-                    for (int s = 0; s < 8; ++s) {
-                        const double dx = xs[s & 1 ? D.N[0] - 1 - X : X] - xs[xq];
-                        const double dy = ys[s & 2 ? D.N[1] - 1 - Y : Y] - ys[yq];
-                        const double dz = zs[s & 4 ? D.N[2] - 1 - Z : Z] - zs[zq];
-                        bad[s] = fma(a, inv_dist<true>(fma(dx, dx, fma(dy, dy, dz * dz)), drop2), bad[s]);
-                    }
-                }
-        if (any)
-            for (int s = 0; s < 8; ++s) v[s] = 8.0 * bad[s];
+    if (threadIdx.x == 0) terms = 0;
+    if (__syncthreads_or(!finite)) {
+        const double *fa = f ? f + src * ndof : phi + pi[src] * ndof, *fb = f ? nullptr : phi + pj[src] * ndof;
+        int mine = 0;
+#pragma unroll 4
+        for (long long q = threadIdx.x; q < ndof; q += 256) {
+            double a = fa[q];
+            if (fb) a *= fb[q];
+            if (fabs(a) < 1e200) continue;  // the product with its weight is finite
+            const int n3 = n * n * n, l = (int)(q % n3);
+            a *= dev->ax[0].m[l % n] * dev->ax[1].m[l / n % n] * dev->ax[2].m[l / (n * n)];
+            mine |= isnan(a) ? NAN_ : !isinf(a) ? 0 : a > 0.0 ? POS : NEG;
+        }
+        if (mine) atomicOr(&terms, mine);
+        __syncthreads();
+        if (terms && !finite) {
+            const double inf = terms == POS ? INFINITY : terms == NEG ? -INFINITY : NAN;
+            for (int s = 0; s < 8; ++s) {
+                const int x0 = s & 1 ? D.N[0] - 1 - X : X, y0 = s & 2 ? D.N[1] - 1 - Y : Y,
+                          z0 = s & 4 ? D.N[2] - 1 - Z : Z;
+                v[s] = inf;
+                // the nodes at the same place: the node itself and those of the neighbour elements
+                for (int z = max(z0 - 1, 0); z <= min(z0 + 1, D.N[2] - 1); ++z)
+                    for (int y = max(y0 - 1, 0); y <= min(y0 + 1, D.N[1] - 1); ++y)
+                        for (int x = max(x0 - 1, 0); x <= min(x0 + 1, D.N[0] - 1); ++x) {
+                            const double dx = xs[x0] - xs[x], dy = ys[y0] - ys[y], dz = zs[z0] - zs[z];
+                            if (!(fma(dx, dx, fma(dy, dy, dz * dz)) > drop2) &&
+                                isinf(quad_source(src, x, y, z, D, n, ndof, dev, f, phi, pi, pj)))
+                                v[s] = NAN;
+                        }
+            }
+        }
     }
+    if (own >= D.nbo) return;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) g[(long long)(r0 + r) * nface + face_slot(fc, X, Y, Z, s, D)] = 0.125 * v[s];
+    for (int s = 0; s < 8; ++s) g[(long long)src * nface + face_slot(fc, X, Y, Z, s, D)] = 0.125 * v[s];
 }
 
 }  // namespace
@@ -591,8 +612,8 @@ void launch_quad_data(const LevelHost& L, const LevelDev<double>* dev, const dou
             default: throw std::logic_error("no quadrature kernel for this tile");
         }
         const int nr = std::min(T.R, left);
-        hipLaunchKernelGGL(k_quad_combine, dim3((unsigned)(((long long)nr * D.nbo + 255) / 256)), dim3(256), 0, s, out,
-                           T.S, T.R, D, nface, nr, r0, dev, L.n, L.ndof, xs, ys, zs, drop2, f, phi, pi, pj, g);
+        hipLaunchKernelGGL(k_quad_combine, dim3((unsigned)((D.nbo + 255) / 256), (unsigned)nr), dim3(256), 0, s, out,
+                           T.S, T.R, D, nface, r0, dev, L.n, L.ndof, xs, ys, zs, drop2, f, phi, pi, pj, g);
         r0 += nr;
     }
 }

@@ -87,6 +87,51 @@ def test_boundary_data_of_values_that_are_not_finite(gpu_lib, nsrc):
     assert np.array_equal(g[2:], ref[2:])
 
 
+@pytest.mark.parametrize("nsrc", [2, 6])
+def test_boundary_data_of_values_that_are_not_finite_on_a_large_mesh(gpu_lib, nsrc):
+    """512,000 nodes, one value of a source infinite, then all of them, then NaN: the values of the
+    plain sum (an infinite value at the boundary node itself, whose term is left out, gives NaN there and
+    nowhere else), the other source untouched, in no more than ten times the time of finite values."""
+    import torch
+    ctx = gpu_lib.Context([((16, 16, 16), 4, [-8.0] * 3, [8.0] * 3)], lanes=1)
+    nd = ctx.info[0]["n_dofs"]
+    f = torch.as_tensor(np.random.default_rng(8).standard_normal((nsrc, nd))).cuda()
+
+    def run():
+        ms = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            g = ctx.boundary_data(f.reshape(-1)).reshape(nsrc, -1)
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b))
+        return g, min(ms[1:])
+
+    ref, t0 = run()
+    times = {}
+    for what, value, where in (("inner", np.inf, slice(200062, 200063)), ("corner", -np.inf, slice(0, 1)),
+                               ("all", np.inf, slice(None)), ("nan", np.nan, slice(77, 78))):
+        keep = f[0].clone()
+        f[0, where] = value
+        g, times[what] = run()
+        f[0] = keep
+        assert torch.equal(g[1:], ref[1:])
+        if what == "inner":
+            assert bool((g[0] == np.inf).all())
+        elif what == "corner":   # the mesh's first node: the first of its x, y and z faces
+            n = 80 * 80
+            own = [0, 2 * n, 4 * n]
+            assert bool(torch.isnan(g[0][own]).all())
+            g[0][own] = -np.inf
+            assert bool((g[0] == -np.inf).all())
+        else:
+            assert bool(torch.isnan(g[0]).all())
+    print("finite %.3f ms, not finite %s" % (t0, {k: round(v, 3) for k, v in times.items()}))
+    assert max(times.values()) <= 10.0 * t0, (t0, times)
+    ctx.close()
+
+
 def test_boundary_data_zero_sources_and_errors(gpu_lib):
     import torch
     ctx = gpu_lib.Context([((2, 2, 2), 2, [-1.0] * 3, [1.0] * 3)])
