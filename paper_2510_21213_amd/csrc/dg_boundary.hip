@@ -42,10 +42,10 @@
 // at a time: they stream the same records through its L2.
 //
 // Measured (36 pair densities of 16^3 elements, p = 4; 38,400 boundary nodes x 512,000
-// grid nodes): 6.5 ms for the whole call, 33.5 ms as a plain sum over all nodes; one density
-// 1.63 ms against 6.8.  16 sources take 2.8 ms, 32 4.6, 4 1.9: a pass costs about 1.5 ms of
-// inverse distances (83 FP64 instructions and 8 reciprocal roots per pair) and 0.10 (vector) or
-// 0.11 ms (matrix, of the padded width) a source; the FP64 vector and matrix instructions do not
+// grid nodes): 6.0 ms for the whole call, 33.5 ms as a plain sum over all nodes; one density
+// 1.26 ms against 6.8.  16 sources take 2.7 ms, 4 1.6: a pass costs about 1.2 ms of
+// inverse distances (83 FP64 instructions and 8 reciprocal roots per pair) and 0.10 ms a source (of
+// the padded width on the matrix unit); the FP64 vector and matrix instructions do not
 // overlap, so the sum of the two bounds it.
 // Tried: 48 and 64 sources a tile (one wave per SIMD: 9.7 and 28 ms), K of the next step formed
 // between the matrix instructions (no faster: 6.5 ms).
@@ -74,9 +74,14 @@ constexpr int quad_tile(int left, int rmax) {
     if (left > QUAD_VEC && rmax >= 16) return 16;
     return left < QUAD_VEC ? (left < rmax ? left : rmax) : (rmax < QUAD_VEC ? rmax : QUAD_VEC);
 }
-// Waves a launch aims for: two to four rounds of those that fit at once (5 to 8 per SIMD in the vector
-// kernel, which waits on scalar loads; 2 or 3 in the matrix kernel), so that a last round costs little.
-constexpr int QUAD_WAVES_VEC = 16384, QUAD_WAVES_MFMA = 8192;
+// Parts the octant is split into: 64, of at least 80 nodes, and fewer where the boundary alone gives the waves
+// (of 64 octant boundary nodes).  One number for both kernels (quad_parts).  The whole call with 48 / 64 / 80 / 100
+// parts, and before with 8,192 work-group waves for the matrix kernel and 16,384 for the vector kernel: 16^3
+// elements p = 4, 1 source 1.30 / 1.26 / 1.25 / 1.35 ms (1.50), 16 sources 2.75 / 2.69 / 2.78 / 2.89 (2.77), 36
+// 6.11 / 5.98 / 6.08 / 6.31 (6.48); 8^3 x 8 0.23 / 0.26 / 0.29 / 0.35 (0.35); 12^3 x 1 0.50 / 0.45 / 0.49 / 0.53
+// (0.98); 20^3 x 2 3.93 / 3.91 / 3.91 / 3.90 (3.81); 24^3 x 3 10.7 / 9.8 / 10.1 / 10.1 (9.9); 32^3 x 12, cut by
+// the waves, 73 (87; at 4,096 waves 81).
+constexpr int QUAD_PARTS = 64, QUAD_PART_NODES = 80, QUAD_WAVES = 12288;
 constexpr int QUAD_CHUNK = 8;      // octant nodes per LDS stage of the matrix kernel (two MFMA steps)
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -306,7 +311,7 @@ __global__ __launch_bounds__(QUAD_BLOCK, 2) void k_quad_mfma(const double* __res
                                                              const double* __restrict__ zs, QuadDims D, int nface,
                                                              int nper, int ntb, double drop2,
                                                              const double* __restrict__ rec,
-                                                             double* __restrict__ out) {
+                                                             double* __restrict__ out, int nr) {
     constexpr int R = 16 * NT, NV = 8 * R;               // values of a node's record
     constexpr int NS = NV + 16;                          // its LDS stride: two nodes fall on different banks
     constexpr int LD = QUAD_CHUNK * NV / (2 * QUAD_BLOCK);  // double2 a thread stages per chunk
@@ -393,10 +398,12 @@ __global__ __launch_bounds__(QUAD_BLOCK, 2) void k_quad_mfma(const double* __res
         const int b = b0 + kq + 4 * i;
         if (b >= D.nbo) continue;
 #pragma unroll
-        for (int n = 0; n < NT; ++n)
+        for (int n = 0; n < NT; ++n) {
+            if (n * 16 + m >= nr) continue;
 #pragma unroll
             for (int s = 0; s < 8; ++s)
-                store_parity(out + ((long long)part * R + n * 16 + m) * nface, b, s, D, acc[s][n][i]);
+                store_parity(out + ((long long)part * nr + n * 16 + m) * nface, b, s, D, acc[s][n][i]);
+        }
     }
 }
 
@@ -508,30 +515,29 @@ double* quad_scratch(int device, long long* capacity) {
 
 namespace {
 
-// Most parts the octant is split into for tiles of R sources.  The same for every width of the vector
-// kernel, so that a source's data do not depend on how many share its call there.
-int quad_parts(const QuadDims& D, int R) {
-    const bool vec = R <= QUAD_VEC;
-    const long long waves = (D.nbo + (vec ? QUAD_BLOCK : 64) - 1) / (vec ? QUAD_BLOCK : 64) * (QUAD_BLOCK / 64);
-    const long long want = ((vec ? QUAD_WAVES_VEC : QUAD_WAVES_MFMA) + waves - 1) / waves;
-    return (int)std::max(1LL, std::min<long long>((D.noct + 63) / 64, want));  // at least 64 nodes a part
+// Parts of the octant: by the mesh alone, so that a source's data do not depend on the others of its call.
+// (v_mfma_f64_16x16x4 adds its four products one after the other, each rounded as a fused multiply-add: the
+// vector and the matrix kernel give the same sums of a part, bit for bit.)
+int quad_parts(const QuadDims& D) {
+    const int waves = (D.nbo + 63) / 64;
+    return std::max(1, std::min({D.noct / QUAD_PART_NODES, QUAD_PARTS, QUAD_WAVES / waves}));
 }
 
-// One pass over the octant: source tile, nodes per part, parts (at most `most`).
+// One pass over the octant: source tile, the sources in it, nodes per part, parts (at most `most`).  One part
+// leaves its sums in g itself.
 struct QuadPass {
-    int R, nper, S;
+    int R, nr, nper, S;
 };
 QuadPass quad_pass(const QuadDims& D, int left, int rmax, long long part_len, long long nface) {
     QuadPass T{};
     T.R = quad_tile(left, rmax);
-    const long long most = std::max(1LL, std::min<long long>(quad_parts(D, T.R), part_len / (T.R * nface)));
+    T.nr = std::min(T.R, left);
+    const long long most = std::max(1LL, std::min<long long>(quad_parts(D), part_len / (T.nr * nface)));
     const int nper = (int)((D.noct + most - 1) / most);
     T.nper = (nper + QUAD_CHUNK - 1) / QUAD_CHUNK * QUAD_CHUNK;
     T.S = (D.noct + T.nper - 1) / T.nper;
     return T;
 }
-// One part of a tile that pads no source leaves its sums in g itself; everything else needs part space.
-bool quad_direct(const QuadPass& T, int left) { return T.S == 1 && T.R <= left; }
 
 // The plan with source tiles of at most rmax in `capacity` doubles; rmax = 0 when it does not fit.
 QuadPlan quad_plan_width(const LevelHost& L, int nsrc, int rmax, long long capacity) {
@@ -541,14 +547,13 @@ QuadPlan quad_plan_width(const LevelHost& L, int nsrc, int rmax, long long capac
     for (int left = nsrc; left > 0; left -= quad_tile(left, rmax)) {
         const int R = quad_tile(left, rmax);
         P.rec_len = std::max(P.rec_len, 8LL * D.noct * R);
-        P.part_len = std::max(P.part_len, (long long)quad_parts(D, R) * R * P.nface);
+        P.part_len = std::max(P.part_len, (long long)quad_parts(D) * std::min(R, left) * P.nface);
     }
     if (P.rec_len > capacity) return P;
     P.part_len = std::min(P.part_len, capacity - P.rec_len);
     P.wgs = 1LL << 40;
     for (int left = nsrc; left > 0; left -= quad_tile(left, rmax)) {
         const QuadPass T = quad_pass(D, left, rmax, P.part_len, P.nface);
-        if (!quad_direct(T, left) && (long long)T.S * T.R * P.nface > P.part_len) return P;
         const int per = T.R <= QUAD_VEC ? QUAD_BLOCK : 64;
         P.wgs = std::min(P.wgs, (long long)T.S * ((D.nbo + per - 1) / per));
     }
@@ -595,8 +600,8 @@ void launch_quad_data(const LevelHost& L, const LevelDev<double>* dev, const dou
     for (int r0 = 0; r0 < nsrc;) {
         const int left = nsrc - r0;
         const QuadPass T = quad_pass(D, left, P.rmax, P.part_len, P.nface);
-        const bool direct = quad_direct(T, left), vec = T.R <= QUAD_VEC;
-        if (8LL * D.noct * T.R > P.rec_len || (!direct && (!part || (long long)T.S * T.R * nface > P.part_len)))
+        const bool direct = T.S == 1, vec = T.R <= QUAD_VEC;
+        if (8LL * D.noct * T.R > P.rec_len || (!direct && (!part || (long long)T.S * T.nr * nface > P.part_len)))
             throw std::logic_error("quadrature plan does not fit the mesh");
         const int per = vec ? QUAD_BLOCK : 64, ntb = (D.nbo + per - 1) / per;
         if ((long long)ntb * T.S >= (1LL << 31)) throw std::logic_error("quadrature grid too large");
@@ -604,17 +609,19 @@ void launch_quad_data(const LevelHost& L, const LevelDev<double>* dev, const dou
                            dim3(PACK_NODES * PACK_SRC), 0, s, dev, D, L.n, L.ndof, nsrc, r0, T.R, f, phi, pi, pj, rec);
         double* out = direct ? g + (long long)r0 * nface : part;
         switch (T.R) {
-#define QUAD_CASE(K, RR) \
-    case RR: hipLaunchKernelGGL(K, dim3((unsigned)(ntb * T.S)), dim3(QUAD_BLOCK), 0, s, xs, ys, zs, D, nface, T.nper, ntb, drop2, rec, out); break;
-            QUAD_CASE(k_quad<1>, 1) QUAD_CASE(k_quad<2>, 2) QUAD_CASE(k_quad<3>, 3) QUAD_CASE(k_quad<4>, 4)
-            QUAD_CASE(k_quad_mfma<1>, 16) QUAD_CASE(k_quad_mfma<2>, 32)
+#define QUAD_CASE(RR, K, ...)                                                                                       \
+    case RR:                                                                                                       \
+        hipLaunchKernelGGL(K, dim3((unsigned)(ntb * T.S)), dim3(QUAD_BLOCK), 0, s, xs, ys, zs, D, nface, T.nper, ntb, \
+                           drop2, rec, out __VA_ARGS__);                                                           \
+        break;
+            QUAD_CASE(1, k_quad<1>) QUAD_CASE(2, k_quad<2>) QUAD_CASE(3, k_quad<3>) QUAD_CASE(4, k_quad<4>)
+            QUAD_CASE(16, k_quad_mfma<1>, , T.nr) QUAD_CASE(32, k_quad_mfma<2>, , T.nr)
 #undef QUAD_CASE
             default: throw std::logic_error("no quadrature kernel for this tile");
         }
-        const int nr = std::min(T.R, left);
-        hipLaunchKernelGGL(k_quad_combine, dim3((unsigned)((D.nbo + 255) / 256), (unsigned)nr), dim3(256), 0, s, out,
-                           T.S, T.R, D, nface, r0, dev, L.n, L.ndof, xs, ys, zs, drop2, f, phi, pi, pj, g);
-        r0 += nr;
+        hipLaunchKernelGGL(k_quad_combine, dim3((unsigned)((D.nbo + 255) / 256), (unsigned)T.nr), dim3(256), 0, s, out,
+                           T.S, T.nr, D, nface, r0, dev, L.n, L.ndof, xs, ys, zs, drop2, f, phi, pi, pj, g);
+        r0 += T.nr;
     }
 }
 

@@ -132,6 +132,22 @@ def test_boundary_data_of_values_that_are_not_finite_on_a_large_mesh(gpu_lib, ns
     ctx.close()
 
 
+@pytest.mark.parametrize("E,p", [((12, 12, 12), 4), ((7, 4, 5), 3), ((5, 3, 3), 2)])
+def test_a_source_has_the_same_data_in_every_batch(gpu_lib, E, p):
+    """Alone (vector kernel), among four, and in batches of 5 to 37 sources (matrix tiles of 16 and 32,
+    full and padded, a last vector pass): the same bits."""
+    import torch
+    ctx = gpu_lib.Context([(E, p, [0.0, -1.0, 0.5], [3.0, 2.0, 2.5])])
+    nd = ctx.info[0]["n_dofs"]
+    f = torch.as_tensor(np.random.default_rng(3).standard_normal((37, nd))).cuda()
+    ref = ctx.boundary_data(f.reshape(-1)).reshape(37, -1)
+    for n in (1, 2, 3, 4, 5, 16, 17, 20, 32, 33, 36):
+        for first in (0, 37 - n):
+            g = ctx.boundary_data(f[first:first + n].reshape(-1)).reshape(n, -1)
+            assert torch.equal(g, ref[first:first + n]), (n, first)
+    ctx.close()
+
+
 def test_boundary_data_zero_sources_and_errors(gpu_lib):
     import torch
     ctx = gpu_lib.Context([((2, 2, 2), 2, [-1.0] * 3, [1.0] * 3)])
