@@ -563,8 +563,25 @@ QuadPlan quad_plan_width(const LevelHost& L, int nsrc, int rmax, long long capac
 
 }  // namespace
 
+// The kernels' indices of octant nodes and of a face vector are 32-bit.
+bool quad_indices_fit(const LevelHost& L) {
+    long long N[3], noct = 1;
+    for (int k = 0; k < 3; ++k) {
+        N[k] = (long long)L.E[k] * L.n;
+        noct *= (N[k] + 1) / 2;
+    }
+    return noct <= (1LL << 30) && 2 * (N[2] * N[1] + N[2] * N[0] + N[1] * N[0]) <= (1LL << 30);
+}
+
+// The widest tiles, whose padding may cost memory on a large grid (5 sources take the records of 16): beyond
+// 8 GiB the records hold no more than a number of fields that follows the sources (in fours, at most 48).
 QuadPlan quad_plan(const LevelHost& L, int nsrc) {
-    return quad_plan_width(L, nsrc, 32, 1LL << 60);
+    const long long fields = nsrc < 4 ? nsrc : std::min(48, (nsrc + 3) / 4 * 4);
+    for (int rmax : {32, 16}) {
+        const QuadPlan P = quad_plan_width(L, nsrc, rmax, 1LL << 60);
+        if (P.rec_len <= std::max(1LL << 30, L.ndof * fields)) return P;
+    }
+    return quad_plan_width(L, nsrc, QUAD_VEC, 1LL << 60);
 }
 
 // A plan whose records and partial sums fit in `capacity` doubles: the widest source tile that
@@ -591,7 +608,7 @@ void launch_quad_data(const LevelHost& L, const LevelDev<double>* dev, const dou
     if (nsrc <= 0) return;
     const QuadDims D = quad_dims(L);
     const long long nfaces = 2 * ((long long)D.N[2] * D.N[1] + (long long)D.N[2] * D.N[0] + (long long)D.N[1] * D.N[0]);
-    if (P.nface != nfaces || nfaces > (1LL << 30) || L.ndof > (1LL << 30) || P.rmax < 1)
+    if (P.nface != nfaces || P.rmax < 1 || !quad_indices_fit(L))
         throw std::logic_error("quadrature plan does not fit the mesh");
     const double hmin = std::min({L.h[0], L.h[1], L.h[2]});
     const double drop2 = (1e-6 * hmin) * (1e-6 * hmin);

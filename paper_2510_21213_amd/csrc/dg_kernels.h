@@ -293,6 +293,8 @@ struct QuadPlan {
     long long nface, rec_len, part_len, wgs;  // wgs: the fewest work-groups of a pass
 };
 QuadPlan quad_plan(const LevelHost& L, int nsrc);
+// Whether the mesh is within launch_quad_data's index range.
+bool quad_indices_fit(const LevelHost& L);
 // The same with rec_len + part_len <= capacity doubles (rmax = 0 if the mesh cannot fit).
 QuadPlan quad_plan_bounded(const LevelHost& L, int nsrc, long long capacity);
 // The fixed work space of dg_boundary_data_noalloc (a file-scope device array): look up this
