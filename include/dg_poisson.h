@@ -286,7 +286,8 @@ dg_status dg_boundary_data_noalloc(dg_ctx* ctx, int mesh_id, int nsrc, const dou
  * Functions on the grid are element-major fields of the mesh's finest level, packed one after
  * another ([count][n_dofs], device).  Integrals use the grid's quadrature rule (Sec. 6.1:
  * each factor evaluated at the nodes, weights = the lumped GLL mass).  Outputs are row-major
- * device matrices.  Work is enqueued on `stream` (no synchronisation unless stated). */
+ * device matrices; an entry of a projection is the same bits whatever else the call forms.  Work
+ * is enqueued on `stream` (no synchronisation unless stated). */
 
 /* Hartree action on vectors u_a projected on basis functions phi_i (Sec. 6.1, the action of
  * eq. hartreecoulomb on an orbital): out[i*nu + a] = sum over nodes of w phi_i u_a vH, where vH

@@ -1923,7 +1923,7 @@ namespace {
 // out = quadrature projection (phi_i, f u_a) on the mesh's finest level, on stream s.
 void project(dg_ctx* ctx, Mesh& M, int nbasis, const double* phi, int nu, const double* u, const double* f,
              double* out, hipStream_t s) {
-    ensure_len(ctx->cpart, ctx->cpart_cap, (long long)nbasis * nu * dg::project_chunks(M.lv[0].ndof, nbasis, nu));
+    ensure_len(ctx->cpart, ctx->cpart_cap, dg::project_partials(M.lv[0].ndof, nbasis, nu));
     dg::launch_project(M.lv[0], nbasis, phi, nu, u, f, ctx->cpart, out, s);
 }
 

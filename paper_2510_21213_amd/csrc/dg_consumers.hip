@@ -20,8 +20,12 @@ namespace {
 
 constexpr int PJ_THREADS = 256;
 constexpr int PJ_MAXN3 = 512;  // nodes per element (degree <= 7)
-constexpr int PJ_WGS = 512;    // work-groups of a launch: all resident at once (256 x 8 projections and the
-                               // compressed exchange's, whole calls: 0.65 ms, 0.69 at 1024, 0.665 at 2048)
+// Chunks of a field: by the mesh alone, so that an entry's sum does not depend on how many are formed with it.
+// Whole calls with 192 / 256 / 384 / 512 chunks and, before, about 512 work-groups a launch: 256 x 8 entries on
+// 512,000 nodes 0.232 / 0.280 / 0.240 / 0.262 ms (0.267), 8 x 8 0.062 / 0.055 / 0.053 / 0.051 (0.050), 64 x 8 on
+// 4,096,000 nodes 0.86 / 0.67 / 0.62 / 0.51 (0.51), 1000 x 4 on 960,000 1.38 / 1.41 / 1.45 / 1.49 (1.56).
+constexpr int PJ_CHUNKS = 512;
+constexpr long long PJ_PARTIAL = 1LL << 28;  // doubles of partial sums a launch may take: more go row block by row block
 
 // 16 bytes of a field whose rows start at any multiple of 8
 typedef double pj_d2 __attribute__((ext_vector_type(2), aligned(8)));
@@ -231,31 +235,37 @@ __global__ __launch_bounds__(256) void k_small_gemm(int ni, int nk, int na, cons
 // where a launch needs the work-groups more than the saved reads of u.
 static int project_rows(int nbasis) { return nbasis > 16 ? 64 : 16; }
 
-// Nodes of a chunk, in whole steps of the work-group's four waves: PJ_WGS work-groups.
-static long long project_nodes(long long ndof, int nbasis, int nu) {
-    const int rows = project_rows(nbasis);
-    const long long tiles = (long long)((nbasis + rows - 1) / rows) * ((nu + 15) / 16);
-    const long long most = std::max(1LL, PJ_WGS / tiles);
-    return std::max(256LL, ((ndof + most - 1) / most + 63) / 64 * 64);
+// Nodes of a chunk, in whole steps of the work-group's four waves.
+static long long project_nodes(long long ndof) {
+    return std::max(256LL, ((ndof + PJ_CHUNKS - 1) / PJ_CHUNKS + 63) / 64 * 64);
+}
+static long long project_chunks(long long ndof) { return (ndof + project_nodes(ndof) - 1) / project_nodes(ndof); }
+
+// Rows of phi of a launch: all, or whole tiles whose partial sums fit.
+static int project_pass(long long ndof, int nbasis, int nu) {
+    const long long rows = PJ_PARTIAL / (nu * project_chunks(ndof)) / 64 * 64;
+    return (int)std::min<long long>(nbasis, std::max(64LL, rows));
 }
 
-int project_chunks(long long ndof, int nbasis, int nu) {
-    const long long cn = project_nodes(ndof, nbasis, nu);
-    return (int)((ndof + cn - 1) / cn);
+long long project_partials(long long ndof, int nbasis, int nu) {
+    return project_pass(ndof, nbasis, nu) * project_chunks(ndof) * nu;
 }
 
 void launch_project(const LevelHost& L, int nbasis, const double* phi, int nu, const double* u, const double* f,
                     double* partial, double* out, hipStream_t s) {
     if (nbasis == 0 || nu == 0) return;
     if (L.ndof >= 0x7fffffffLL || L.n * L.n * L.n > PJ_MAXN3) throw std::runtime_error("projection: field too large");
-    const int nchunk = project_chunks(L.ndof, nbasis, nu), cn = (int)project_nodes(L.ndof, nbasis, nu);
-    const int rows = project_rows(nbasis);
-    const long long grid = (long long)((nbasis + rows - 1) / rows) * ((nu + 15) / 16) * nchunk;
-    if (grid > 0x7fffffffLL) throw std::runtime_error("projection grid too large");
-    auto* k = rows == 64 ? k_project<4> : k_project<1>;
-    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(PJ_THREADS), 0, s, L.dev64, L.n, (int)L.ndof, nbasis, phi, nu, u,
-                       f, nchunk, cn, partial);
-    launch_sum_partials(nbasis * nu, partial, nchunk, nchunk, out, s);
+    const int nchunk = (int)project_chunks(L.ndof), cn = (int)project_nodes(L.ndof);
+    const int pass = project_pass(L.ndof, nbasis, nu);
+    for (int i = 0; i < nbasis; i += pass) {
+        const int nb = std::min(pass, nbasis - i), rows = project_rows(nb);
+        const long long grid = (long long)((nb + rows - 1) / rows) * ((nu + 15) / 16) * nchunk;
+        if (grid > 0x7fffffffLL) throw std::runtime_error("projection grid too large");
+        auto* k = rows == 64 ? k_project<4> : k_project<1>;
+        hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(PJ_THREADS), 0, s, L.dev64, L.n, (int)L.ndof, nb,
+                           phi + i * L.ndof, nu, u, f, nchunk, cn, partial);
+        launch_sum_partials(nb * nu, partial, nchunk, nchunk, out + (long long)i * nu, s);
+    }
 }
 
 void launch_cross_products(long long ndof, int nu, int nocc, const double* u, const double* psi, double* rho,

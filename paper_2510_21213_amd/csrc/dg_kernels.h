@@ -265,9 +265,8 @@ void launch_group_pcg(const FusedMeshDev* M, int K, int nrhs, const double* b, d
 // Consumers of the grid potentials (dg_consumers.hip).  Quadrature weight of a node: the product
 // of the level's three 1D lumped masses.
 // out[i * nu + a] = sum_q w_q f_q phi_i(q) u_a(q) over the nodes of level L (f null: 1), fields
-// packed [nbasis][ndof] and [nu][ndof]; partial: nbasis * nu * project_chunks(L.ndof, nbasis, nu)
-// doubles.
-int project_chunks(long long ndof, int nbasis, int nu);
+// packed [nbasis][ndof] and [nu][ndof]; partial: project_partials(L.ndof, nbasis, nu) doubles.
+long long project_partials(long long ndof, int nbasis, int nu);
 void launch_project(const LevelHost& L, int nbasis, const double* phi, int nu, const double* u, const double* f,
                     double* partial, double* out, hipStream_t s);
 // rho[a * nocc + s] = u_a psi_s

@@ -69,6 +69,35 @@ def test_projection_tile_edges_match_oracle(gpu_lib, E, p, nb, nu):
     ctx.close()
 
 
+@pytest.mark.parametrize("E,p", [((16, 16, 16), 4), ((5, 3, 7), 3)])
+def test_an_entry_has_the_same_bits_in_every_projection(gpu_lib, E, p):
+    """Parts of a 150 x 20 projection (row tiles of 16 and 64, one or two vector tiles) by themselves."""
+    import torch
+    ctx = gpu_lib.Context([(E, p, (-1.0, -2.0, -1.5), (2.0, 1.0, 1.5))], lanes=1)
+    nd = ctx.info[0]["n_dofs"]
+    rng = np.random.default_rng(7)
+    phi, u, vH = _t(rng.standard_normal((150, nd))), _t(rng.standard_normal((20, nd))), _t(rng.standard_normal(nd))
+    ref = ctx.hartree_action(phi, u, vH)
+    for i0, i1, a0, a1 in ((0, 1, 0, 1), (3, 19, 0, 16), (140, 150, 19, 20), (0, 64, 2, 19), (21, 150, 5, 6)):
+        got = ctx.hartree_action(phi[i0:i1].contiguous(), u[a0:a1].contiguous(), vH)
+        assert torch.equal(got, ref[i0:i1, a0:a1]), (i0, i1, a0, a1)
+    ctx.close()
+
+
+def test_projection_in_several_launches(gpu_lib):
+    """15,000 x 1,024 entries over 32 chunks: the partial sums go in two launches of 8,192 and 6,808 rows."""
+    import torch
+    ctx = gpu_lib.Context([((4, 4, 4), 4, (-1.0, -2.0, -1.5), (2.0, 1.0, 1.5))], lanes=1)
+    nd = ctx.info[0]["n_dofs"]
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    phi, u, vH = (torch.randn(k, nd, dtype=torch.float64, device="cuda", generator=gen) for k in (15000, 1024, 1))
+    got = ctx.hartree_action(phi, u, vH[0])
+    for i0, i1, a0, a1 in ((0, 3, 0, 5), (8190, 8195, 1020, 1024), (14999, 15000, 511, 513)):
+        part = ctx.hartree_action(phi[i0:i1].contiguous(), u[a0:a1].contiguous(), vH[0])
+        assert torch.equal(got[i0:i1, a0:a1], part), (i0, a0)
+    ctx.close()
+
+
 def _orbitals():
     prims = gaussians.Primitives([0.6, 1.4, 0.9, 0.45], [[0.4, 0, 0], [0.4, 0, 0], [-0.5, 0.2, 0.1],
                                                           [-0.5, 0.2, 0.1]])
