@@ -856,7 +856,13 @@ void conv_forward_mfma(const dg_net* net, int li, const TX* x, TY* y, int B, con
             maxbox = std::max(maxbox, bx.bz * bx.by * bx.bx);
         }
         const size_t lds = (size_t)maxbox * 64;
-        if (lds > 64 * 1024) throw NetError("convolution input box too large for LDS");
+        // A work-group's voxels that lie on two planes need the whole of both: where that does not fit the
+        // 64 KB of a launch (large planes of no multiple of 128 voxels, 24^3: 173 KB), the form without LDS.
+        // Forward pass of four levels and 32 channels: 24^3 x 4 0.54 ms, 22^3 x 4 0.49, 32^3 x 2 (staged) 0.43.
+        if (lds > 64 * 1024) {
+            CMN(3, 1)
+            return;
+        }
         dim3 g3((nvo + CV_VPW - 1) / CV_VPW, B);
 #define C3(NBV) hipLaunchKernelGGL((k_conv3_lds<NBV, TX, TY>), g3, dim3(256), lds, s, x, Wt, b, y, din[0], din[1], din[2], L.ci, CiP, L.co, relu)
         switch (NB) {

@@ -96,6 +96,13 @@ def test_inference_with_bf16_activations(gpu_lib, levels, E, C, cin):
     assert np.abs(y16 - y_ref).max() <= 3e-2 * np.abs(y_ref).max()
 
 
+@pytest.mark.parametrize("levels,E,C,cin", [(4, (24, 24, 24), 8, 27), (2, (20, 25, 3), 32, 27)])
+def test_planes_that_do_not_fit_the_staged_convolution(gpu_lib, levels, E, C, cin):
+    """Planes of more than a few hundred voxels, no multiple of the 128 of a work-group: a work-group's
+    voxels cross planes and their input box exceeds its LDS."""
+    test_inference_with_bf16_activations(gpu_lib, levels, E, C, cin)
+
+
 def _continuize_1d(E, n):
     """1D averaging of the two copies of every node shared by neighbouring elements."""
     N = E * n
