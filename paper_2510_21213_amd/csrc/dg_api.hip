@@ -122,14 +122,18 @@ struct dg_ctx {
         dg::RhsState* st_host = nullptr; // pinned host mirror
         int cap_b = 0, cap_st = 0;
         // captured PCG iterations, per kind of run (index 0: FP64, 1: FP32 inner solve, 2: FP32_PC, 3: BF16_PC,
-        // 4: BF16F_PC)
+        // 4: BF16F_PC), and one for each of the last chunk targets (LevelHost.wgs: it follows the number of
+        // solves at the same time, so a program that alternates calls of one mesh and of several has a few)
         struct Graph {
             hipGraphExec_t exec = nullptr;
             int nrhs = 0, every = 0, wgs = 0;
             bool prof = false;
             std::vector<hipEvent_t> ev;
             size_t nev = 0;
-        } graph[5];
+            long long used = 0;
+        };
+        std::vector<Graph> graph[5];
+        long long graph_uses = 0;
         // multi-mesh batches: the mesh's own stream and completion event, and its
         // right-hand sides gathered from the caller's packing when they are not contiguous
         hipStream_t stream = nullptr;
@@ -217,10 +221,31 @@ using dg::LevelHost;
 using Mesh = dg_ctx::Mesh;
 
 void drop_graphs(Mesh& M) {
-    for (auto& G : M.graph) {
-        if (G.exec) (void)hipGraphExecDestroy(G.exec);
-        G.exec = nullptr;
+    for (auto& kind : M.graph)
+        for (auto& G : kind) {
+            if (G.exec) (void)hipGraphExecDestroy(G.exec);
+            G.exec = nullptr;
+        }
+}
+
+// The graph of a kind of run for the chunk target wgs (one of another target, the one not used for the
+// longest time, when as many are held).
+Mesh::Graph& graph_of(Mesh& M, int kind, int wgs) {
+    constexpr size_t kHeld = 4;
+    auto& held = M.graph[kind];
+    Mesh::Graph* G = nullptr;
+    for (auto& g : held)
+        if (g.wgs == wgs) G = &g;
+    if (!G && held.size() < kHeld) {
+        held.emplace_back();
+        G = &held.back();
+        G->wgs = wgs;
     }
+    if (!G)
+        G = &*std::min_element(held.begin(), held.end(),
+                               [](const Mesh::Graph& a, const Mesh::Graph& b) { return a.used < b.used; });
+    G->used = ++M.graph_uses;
+    return *G;
 }
 
 void ensure_state(Mesh& M, int nrhs) {
@@ -619,7 +644,7 @@ void pcg_run(dg_ctx* ctx, Mesh& M, Work<T>& W, int nrhs, dg::RhsState* st, const
         // `every` iterations captured once and replayed; an even count keeps the p ping-pong aligned
         int every = std::max(2, ctx->opts.check_every);
         every += every & 1;
-        auto& G = M.graph[kind];
+        auto& G = graph_of(M, kind, L0.wgs);
         if (!G.exec || G.nrhs != nrhs || G.every != every || G.wgs != L0.wgs || G.prof != timed) {
             if (G.exec) (void)hipGraphExecDestroy(G.exec);
             G.exec = nullptr;
@@ -1573,8 +1598,9 @@ void dg_poisson_destroy(dg_ctx* ctx) {
     for (auto e : ctx->prof.ev) (void)hipEventDestroy(e);
     for (auto& M : ctx->meshes) {
         drop_graphs(M);
-        for (auto& G : M.graph)
-            for (auto e : G.ev) (void)hipEventDestroy(e);
+        for (auto& kind : M.graph)
+            for (auto& G : kind)
+                for (auto e : G.ev) (void)hipEventDestroy(e);
     }
     if (ctx->ev_in) (void)hipEventDestroy(ctx->ev_in);
     if (ctx->ev_out) (void)hipEventDestroy(ctx->ev_out);

@@ -60,3 +60,39 @@ def test_chunk_length_does_not_change_a_solution(gpu_lib, precision):
         assert so[0]["iters"] == sb[k]["iters"] == sb[45 + k]["iters"]
         assert np.array_equal(one.cpu().numpy().reshape(-1), big[k]) and np.array_equal(big[k], big[45 + k])
     ctx.close()
+
+
+def test_alternating_calls_of_one_and_several_meshes_keep_their_graphs(gpu_lib):
+    """Calls of one mesh and of three, in turn, with one right-hand side a mesh: the chunk target, and
+    with it the captured iterations, changes from call to call.  A call after one of the other kind takes no
+    longer than after one of its own (solves of two iterations, where a capture takes nearly as long), and
+    solves bit for bit alike."""
+    import time
+
+    import torch
+    wl = configs.scaled(4, 3, 1, seed=17)
+    m = wl.meshes[0]
+    ctx = gpu_lib.Context([(m.E, m.p, m.lo, m.hi)] * 3, lanes=1, rtol=0.3)
+    rho, g = gpu_sample(ctx, 0, wl.batch.densities[0])
+    one = (_t(rho), _t(g), [0])
+    three = (_t(np.tile(rho, 3)), _t(np.tile(g, 3)), [0, 1, 2])
+
+    def run(args):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        v, st = ctx.solve_batch(args[0], args[1], mesh_ids=args[2])
+        torch.cuda.synchronize()
+        return time.perf_counter() - t0, v
+
+    for args in (one, three, one, three):
+        run(args)
+    alone, turn = [], []
+    for _ in range(40):
+        turn.append(run(one))
+        alone.append(run(one))
+        run(three)
+    assert all(torch.equal(v, alone[0][1]) for _, v in alone + turn)
+    a, t = (float(np.median([x for x, _ in r])) for r in (alone, turn))
+    print("after its own kind %.3f ms, after the other %.3f ms" % (1e3 * a, 1e3 * t))
+    assert t <= 1.4 * a
+    ctx.close()
