@@ -990,7 +990,11 @@ __device__ __forceinline__ void mf_xy_terms(const RefDev<float>& R, const mf_s4&
 // Waves per SIMD that the registers are held to where the compiler meets the count or misses it by a
 // few: six (80 VGPRs) for the FP32 smoothing steps of degree 4 on 4x2 tiles (at 81, five waves: 36
 // right-hand sides of 16^3 elements in BF16F_PC 17.6 ms, at 80 16.9), three (168) for the FP64 ones of
-// degrees 4 and 5.  Never below what a step needs: no slab kernel spills.
+// degrees 4 and 5.  Not below what a step needs: no slab kernel spills vector registers (the larger ones
+// keep up to 152 scalars in lanes of a vector register), and the Gauss-Legendre step of degree 5 held at three was
+// compiled wrong: copies of coefficients, made where a live range is split, stood at the head of an if's join
+// in front of the instruction that gives the block its lanes back, so that part of the lanes went on with another
+// value.  tests/test_device_code.py looks for such blocks in the built library.
 template <typename T, int N, int TX, int TY, int MODE, bool MF, bool GL>
 constexpr int slab_waves() {
     if (sizeof(T) == 8 && N == 6 && MODE == BM_CHEB && !GL) return 3;
