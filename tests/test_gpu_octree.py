@@ -98,6 +98,30 @@ def test_operator_work_group_edges_match_oracle(gpu_lib, q, nrhs, rb):
 
 
 @pytest.mark.parametrize("case", CASES)
+def test_a_right_hand_side_has_the_same_bits_in_every_batch(gpu_lib, case):
+    """Products on every level, FP64 and FP32: right-hand sides one or two at a time in a work-group, alone,
+    and in batches of 5 and 67 (two chunks); solves alone and among three."""
+    import torch
+    g, _ = _pair(gpu_lib, case, precision="fp32_pc")
+    rng = np.random.default_rng(23)
+    for level in range(g.n_levels):
+        n = _t(rng.standard_normal((67, g.level_info(level)["n_elements"] * (g.level_info(level)["q"] + 1) ** 3)))
+        for u, op in ((n, g.apply), (n.float(), g.apply_f32)):
+            ref = op(u, level=level).reshape(67, -1)
+            for rb in (1, 2, 4):
+                g.set_rhs_per_block(rb)
+                assert torch.equal(op(u[:5].contiguous(), level=level).reshape(5, -1), ref[:5]), (level, rb)
+            g.set_rhs_per_block(0)
+            for k in (0, 64, 66):
+                assert torch.equal(op(u[k:k + 1].contiguous(), level=level).reshape(-1), ref[k]), (level, k)
+    b = _t(rng.standard_normal((3, g.n_dofs)))
+    x, st = g.solve(b)
+    for k in range(3):
+        one, so = g.solve(b[k:k + 1].contiguous())
+        assert so[0]["iters"] == st[k]["iters"] and torch.equal(one.reshape(-1), x.reshape(3, -1)[k])
+
+
+@pytest.mark.parametrize("case", CASES)
 def test_operator_rhs_bounds_and_vcycle_match_oracle(gpu_lib, case):
     g, t = _pair(gpu_lib, case)
     H = octree.Hierarchy(t)

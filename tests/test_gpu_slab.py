@@ -62,6 +62,26 @@ def test_chunk_length_does_not_change_a_solution(gpu_lib, precision):
     ctx.close()
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32_pc"])
+@pytest.mark.parametrize("E,p,family", [(8, 3, "gll"), (10, 3, "gll"), (8, 5, "gll"), (7, 6, "gll"), (8, 2, "gl"), (8, 3, "gl"),
+                                        (8, 4, "gl"), (6, 5, "gl"), (6, 6, "gl"), (5, 7, "gll")])
+def test_chunk_length_does_not_change_a_solution_of_other_degrees(gpu_lib, E, p, family, precision):
+    """The kernels of the other degrees and of Gauss-Legendre nodes (10^3: the 4x4 tile of degree 3;
+    degree 7: the bricks)."""
+    wl = configs.scaled(E, p, 2, seed=17)
+    m = wl.meshes[0]
+    ctx = gpu_lib.Context([(m.E, m.p, m.lo, m.hi)], precision=precision, lanes=1, node_family=family)
+    rho, g = zip(*[gpu_sample(ctx, 0, d) for d in wl.batch.densities])
+    rho, g = np.concatenate(rho).reshape(2, -1), np.concatenate(g).reshape(2, -1)
+    big, sb = ctx.solve_batch(_t(np.tile(rho, (20, 1))), _t(np.tile(g, (20, 1))))
+    big = big.cpu().numpy().reshape(40, -1)
+    for k in range(2):
+        one, so = ctx.solve_batch(_t(rho[k]), _t(g[k]))
+        assert so[0]["iters"] == sb[k]["iters"] == sb[38 + k]["iters"]
+        assert np.array_equal(one.cpu().numpy().reshape(-1), big[k]) and np.array_equal(big[k], big[38 + k])
+    ctx.close()
+
+
 def test_alternating_calls_of_one_and_several_meshes_keep_their_graphs(gpu_lib):
     """Calls of one mesh and of three, in turn, with one right-hand side a mesh: the chunk target, and
     with it the captured iterations, changes from call to call.  A call after one of the other kind takes no
