@@ -20,18 +20,20 @@ namespace {
 
 constexpr int PJ_THREADS = 256;
 constexpr int PJ_MAXN3 = 512;  // nodes per element (degree <= 7)
-// Chunks of a field: by the mesh alone, so that an entry's sum does not depend on how many are formed with it.
-// Whole calls with 192 / 256 / 384 / 512 chunks and, before, about 512 work-groups a launch: 256 x 8 entries on
-// 512,000 nodes 0.232 / 0.280 / 0.240 / 0.262 ms (0.267), 8 x 8 0.062 / 0.055 / 0.053 / 0.051 (0.050), 64 x 8 on
-// 4,096,000 nodes 0.86 / 0.67 / 0.62 / 0.51 (0.51), 1000 x 4 on 960,000 1.38 / 1.41 / 1.45 / 1.49 (1.56).
-constexpr int PJ_CHUNKS = 512;
+// Chunks of a field: by the mesh alone, and added in pairs of pairs, so that an entry's sum does not depend on
+// how many are formed with it.  A work-group takes 1, 2 or 4 of them, fewer where the launch has few tiles, and
+// adds them itself.  Whole calls, and with about 512 work-groups a launch, each with one chunk of its own size:
+// 256 x 8 entries on 512,000 nodes 0.259 ms (0.266), 8 x 8 0.052 (0.052), 300 x 24 0.529 (0.532), 64 x 8 on
+// 4,096,000 nodes 0.492 (0.508), 1000 x 4 on 960,000 1.42 (1.56).  Tried: always one chunk a work-group (the
+// 8 MB of partial sums of 256 x 8 entries make the first call 0.5 ms longer).
+constexpr int PJ_CHUNKS = 512, PJ_GROUP = 4;
 constexpr long long PJ_PARTIAL = 1LL << 28;  // doubles of partial sums a launch may take: more go row block by row block
 
 // 16 bytes of a field whose rows start at any multiple of 8
 typedef double pj_d2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef double pj_d4 __attribute__((ext_vector_type(4)));
 
-// partial[(i * nu + a) * nchunk + c] = sum over the nodes q of chunk c of w_q f_q phi_i(q) u_a(q),
+// partial[(i * nu + a) * npart + c] = sum over the nodes q of the chunks c g .. c g + g - 1 of w_q f_q phi_i(q) u_a(q),
 // for the 16 RT rows i and the 16 vectors a of this work-group (f null: 1), on
 // v_mfma_f64_16x16x4: a wave takes 16 nodes at a time, a lane four neighbouring ones of its row of
 // phi (lane & 15), so that each row is read in whole 128-byte pieces, and of its vector of u, whose
@@ -48,8 +50,8 @@ template <int RT>
 __global__ __launch_bounds__(PJ_THREADS) void k_project(const LevelDev<double>* __restrict__ Lp, int n, int ndof,
                                                         int nbasis, const double* __restrict__ phi, int nu,
                                                         const double* __restrict__ u, const double* __restrict__ f,
-                                                        int nchunk, int cnodes, double* __restrict__ partial) {
-    __shared__ double red[PJ_THREADS / 64][256];
+                                                        int npart, int g, int cnodes, double* __restrict__ partial) {
+    __shared__ double red[PJ_THREADS / 64][RT * 256];
     __shared__ double wloc[PJ_MAXN3 + 3];
     const int nti = (nbasis + 16 * RT - 1) / (16 * RT), nta = (nu + 15) / 16;
     const int b = blockIdx.x;
@@ -69,66 +71,101 @@ __global__ __launch_bounds__(PJ_THREADS) void k_project(const LevelDev<double>* 
 #pragma unroll
     for (int t = 0; t < RT; ++t) prow[t] = phi + (long long)min(i0 + 16 * t + m, nbasis - 1) * ndof;
     const double* __restrict__ urow = u + (long long)min(a0 + m, nu - 1) * ndof;
-    pj_d4 acc[RT];
+    double one[RT], all[RT];  // sums of the last even chunk, and of the pairs
 #pragma unroll
-    for (int t = 0; t < RT; ++t) acc[t] = pj_d4{0.0, 0.0, 0.0, 0.0};
-    const unsigned qe = min((long long)ndof, (long long)(c + 1) * cnodes);
-    unsigned q = c * cnodes + wv * 16 + 4 * kq;  // the lane's first node
-    int l = q % n3;
+    for (int t = 0; t < RT; ++t) one[t] = all[t] = 0.0;
     const int dl = 64 % n3;
-    for (; q - 4 * kq + 16 <= qe; q += 64) {
-        double pv[RT][4], bv[4];
+    for (int k = 0; k < g; ++k) {
+        pj_d4 acc[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) acc[t] = pj_d4{0.0, 0.0, 0.0, 0.0};
+        const unsigned q0 = (c * g + k) * (unsigned)cnodes, qe = min((long long)ndof, (long long)q0 + cnodes);
+        unsigned q = q0 + wv * 16 + 4 * kq;  // the lane's first node
+        int l = q % n3;
+        for (; q - 4 * kq + 16 <= qe; q += 64) {
+            double pv[RT][4], bv[4];
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const pj_d2 v = *reinterpret_cast<const pj_d2*>(prow[t] + q + 2 * h);
+                    pv[t][2 * h] = v[0];
+                    pv[t][2 * h + 1] = v[1];
+                }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const pj_d2 v = *reinterpret_cast<const pj_d2*>(urow + q + 2 * h);
+                pj_d2 w = {wloc[l + 2 * h], wloc[l + 2 * h + 1]};
+                if (f) w *= *reinterpret_cast<const pj_d2*>(f + q + 2 * h);
+                bv[2 * h] = w[0] * v[0];
+                bv[2 * h + 1] = w[1] * v[1];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[t][j], bv[j], acc[t], 0, 0, 0);
+            l += dl;
+            if (l >= n3) l -= n3;
+        }
+        if (q - 4 * kq < qe) {  // the field's last, incomplete 16 nodes (one wave of the last chunk)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool ok = q + j < qe;
+                const unsigned qq = ok ? q + j : 0;
+                double w = ok ? wloc[l + j] : 0.0;
+                if (f) w *= f[qq];
+                const double bw = w * urow[qq];
+#pragma unroll
+                for (int t = 0; t < RT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(prow[t][qq], bw, acc[t], 0, 0, 0);
+            }
+        }
+        // accumulator: vector = lane & 15, row = lane / 16 + 4 * register
+        if (k) __syncthreads();  // the last chunk's sums are read
 #pragma unroll
         for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const pj_d2 v = *reinterpret_cast<const pj_d2*>(prow[t] + q + 2 * h);
-                pv[t][2 * h] = v[0];
-                pv[t][2 * h + 1] = v[1];
-            }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const pj_d2 v = *reinterpret_cast<const pj_d2*>(urow + q + 2 * h);
-            pj_d2 w = {wloc[l + 2 * h], wloc[l + 2 * h + 1]};
-            if (f) w *= *reinterpret_cast<const pj_d2*>(f + q + 2 * h);
-            bv[2 * h] = w[0] * v[0];
-            bv[2 * h + 1] = w[1] * v[1];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int t = 0; t < RT; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[t][j], bv[j], acc[t], 0, 0, 0);
-        l += dl;
-        if (l >= n3) l -= n3;
-    }
-    if (q - 4 * kq < qe) {  // the field's last, incomplete 16 nodes (one wave of the last chunk)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool ok = q + j < qe;
-            const unsigned qq = ok ? q + j : 0;
-            double w = ok ? wloc[l + j] : 0.0;
-            if (f) w *= f[qq];
-            const double bw = w * urow[qq];
-#pragma unroll
-            for (int t = 0; t < RT; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(prow[t][qq], bw, acc[t], 0, 0, 0);
-        }
-    }
-    // accumulator: vector = lane & 15, row = lane / 16 + 4 * register
-#pragma unroll
-    for (int t = 0; t < RT; ++t) {
-        if (t) __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[wv][(kq + 4 * r) * 16 + m] = acc[t][r];
+            for (int r = 0; r < 4; ++r) red[wv][t * 256 + (kq + 4 * r) * 16 + m] = acc[t][r];
         __syncthreads();
-        const int i = i0 + 16 * t + (threadIdx.x >> 4), a = a0 + (threadIdx.x & 15);
-        if (i < nbasis && a < nu) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
             double s = 0.0;
 #pragma unroll
-            for (int w = 0; w < PJ_THREADS / 64; ++w) s += red[w][threadIdx.x];
-            partial[((long long)i * nu + a) * nchunk + c] = s;
+            for (int w = 0; w < PJ_THREADS / 64; ++w) s += red[w][t * 256 + threadIdx.x];
+            if (k & 1)
+                all[t] += one[t] + s;
+            else
+                one[t] = s;
         }
     }
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const int i = i0 + 16 * t + (threadIdx.x >> 4), a = a0 + (threadIdx.x & 15);
+        if (i < nbasis && a < nu)
+            partial[((long long)i * nu + a) * npart + c] = g == 1 ? one[t] : all[t];
+    }
+}
+
+// out[e] = sum of entry e's partial sums, in pairs of pairs of chunks: a wave an entry.
+__global__ __launch_bounds__(256) void k_project_sum(int ne, int npart, int g, const double* __restrict__ partial,
+                                                     double* __restrict__ out) {
+    constexpr int GROUPS = PJ_CHUNKS / PJ_GROUP;
+    const int lane = threadIdx.x & 63;
+    const long long e = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (e >= ne) return;  // uniform in the wave
+    const double* p = partial + e * npart;
+    auto at = [&](int i) { return i < npart ? p[i] : 0.0; };
+    double s = 0.0;
+#pragma unroll
+    for (int h = 0; h < GROUPS / 64; ++h) {
+        const int c = lane + 64 * h;
+        s += g == 4 ? at(c) : g == 2 ? at(2 * c) + at(2 * c + 1)
+                                     : (at(4 * c) + at(4 * c + 1)) + (at(4 * c + 2) + at(4 * c + 3));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) out[e] = s;
 }
 
 // W[a][q] = sum_s psi[s][q] v[a * nocc + s][q]
@@ -241,30 +278,39 @@ static long long project_nodes(long long ndof) {
 }
 static long long project_chunks(long long ndof) { return (ndof + project_nodes(ndof) - 1) / project_nodes(ndof); }
 
+// Chunks of a work-group: as many as leave the launch about 512 work-groups.
+static int project_group(int nbasis, int nu) {
+    const int rows = project_rows(nbasis);
+    const long long tiles = (long long)((nbasis + rows - 1) / rows) * ((nu + 15) / 16);
+    return tiles >= 4 ? 4 : tiles >= 2 ? 2 : 1;
+}
+static int project_parts(long long ndof, int g) { return (int)((project_chunks(ndof) + g - 1) / g); }
+
 // Rows of phi of a launch: all, or whole tiles whose partial sums fit.
 static int project_pass(long long ndof, int nbasis, int nu) {
-    const long long rows = PJ_PARTIAL / (nu * project_chunks(ndof)) / 64 * 64;
+    const long long rows = PJ_PARTIAL / ((long long)nu * project_parts(ndof, project_group(nbasis, nu))) / 64 * 64;
     return (int)std::min<long long>(nbasis, std::max(64LL, rows));
 }
 
 long long project_partials(long long ndof, int nbasis, int nu) {
-    return project_pass(ndof, nbasis, nu) * project_chunks(ndof) * nu;
+    return (long long)project_pass(ndof, nbasis, nu) * project_parts(ndof, project_group(nbasis, nu)) * nu;
 }
 
 void launch_project(const LevelHost& L, int nbasis, const double* phi, int nu, const double* u, const double* f,
                     double* partial, double* out, hipStream_t s) {
     if (nbasis == 0 || nu == 0) return;
     if (L.ndof >= 0x7fffffffLL || L.n * L.n * L.n > PJ_MAXN3) throw std::runtime_error("projection: field too large");
-    const int nchunk = (int)project_chunks(L.ndof), cn = (int)project_nodes(L.ndof);
+    const int g = project_group(nbasis, nu), npart = project_parts(L.ndof, g), cn = (int)project_nodes(L.ndof);
     const int pass = project_pass(L.ndof, nbasis, nu);
     for (int i = 0; i < nbasis; i += pass) {
         const int nb = std::min(pass, nbasis - i), rows = project_rows(nb);
-        const long long grid = (long long)((nb + rows - 1) / rows) * ((nu + 15) / 16) * nchunk;
+        const long long grid = (long long)((nb + rows - 1) / rows) * ((nu + 15) / 16) * npart;
         if (grid > 0x7fffffffLL) throw std::runtime_error("projection grid too large");
         auto* k = rows == 64 ? k_project<4> : k_project<1>;
         hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(PJ_THREADS), 0, s, L.dev64, L.n, (int)L.ndof, nb,
-                           phi + i * L.ndof, nu, u, f, nchunk, cn, partial);
-        launch_sum_partials(nb * nu, partial, nchunk, nchunk, out + (long long)i * nu, s);
+                           phi + i * L.ndof, nu, u, f, npart, g, cn, partial);
+        hipLaunchKernelGGL(k_project_sum, dim3((unsigned)((nb * nu + 3) / 4)), dim3(256), 0, s, nb * nu, npart, g, partial,
+                           out + (long long)i * nu);
     }
 }
 

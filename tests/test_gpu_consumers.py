@@ -71,7 +71,8 @@ def test_projection_tile_edges_match_oracle(gpu_lib, E, p, nb, nu):
 
 @pytest.mark.parametrize("E,p", [((16, 16, 16), 4), ((5, 3, 7), 3)])
 def test_an_entry_has_the_same_bits_in_every_projection(gpu_lib, E, p):
-    """Parts of a 150 x 20 projection (row tiles of 16 and 64, one or two vector tiles) by themselves."""
+    """Parts of a 150 x 20 projection by themselves: row tiles of 16 and 64, one or two vector tiles, and so
+    work-groups of 1, 2 and 4 chunks."""
     import torch
     ctx = gpu_lib.Context([(E, p, (-1.0, -2.0, -1.5), (2.0, 1.0, 1.5))], lanes=1)
     nd = ctx.info[0]["n_dofs"]
@@ -85,9 +86,9 @@ def test_an_entry_has_the_same_bits_in_every_projection(gpu_lib, E, p):
 
 
 def test_projection_in_several_launches(gpu_lib):
-    """15,000 x 1,024 entries over 32 chunks: the partial sums go in two launches of 8,192 and 6,808 rows."""
+    """15,000 x 1,024 entries with 32 partial sums each: they go in two launches of 8,192 and 6,808 rows."""
     import torch
-    ctx = gpu_lib.Context([((4, 4, 4), 4, (-1.0, -2.0, -1.5), (2.0, 1.0, 1.5))], lanes=1)
+    ctx = gpu_lib.Context([((8, 8, 8), 3, (-1.0, -2.0, -1.5), (2.0, 1.0, 1.5))], lanes=1)
     nd = ctx.info[0]["n_dofs"]
     gen = torch.Generator(device="cuda").manual_seed(4)
     phi, u, vH = (torch.randn(k, nd, dtype=torch.float64, device="cuda", generator=gen) for k in (15000, 1024, 1))
