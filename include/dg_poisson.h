@@ -259,8 +259,10 @@ dg_status dg_pair_densities(long long n_dofs, int norb, int first_pair, int npai
  * [nsrc][n_face] (packed face vectors, face order), written.  The term of a
  * node at the boundary node itself (closer than 1e-6 of the smallest element
  * width) is left out: the method has f vanish on the boundary.  FP64
- * throughout; cost n_face * n_dofs terms per source.  A source's data are the
- * same bits alone and with any others.  Enqueued on `stream`
+ * throughout, to rounding of the largest of a source's data (the box's eight
+ * reflections are summed together); cost n_face * n_dofs terms per source, an
+ * eighth of them formed.  A source's data are the same bits alone and with any
+ * others.  Values that are not finite give the data of the plain sum.  Enqueued on `stream`
  * (no synchronisation); work space is held by the context.  Errors:
  * DG_ERR_ARG for nsrc < 0 or null pointers with nsrc > 0. */
 dg_status dg_boundary_data(dg_ctx* ctx, int mesh_id, int nsrc, const double* f, double* g, hipStream_t stream);

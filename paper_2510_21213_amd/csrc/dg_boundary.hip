@@ -20,7 +20,10 @@
 //     K_s(b, a) = sum_tau chi_s(tau) / |b - tau a|,
 // g(rho b) = 1/8 sum_s chi_s(rho) sum_a K_s(b, a) F_s(a).  A pair (b, a) costs eight
 // inverse distances and 8 multiply-adds per source where the plain sum over its 64
-// images costs 64 of each: an eighth of the work, with the same terms in FP64.
+// images costs 64 of each: an eighth of the work, with the same terms in FP64.  (Rounding is that of the
+// largest of the eight images' values: for densities over the grid that of the plain sum, 2e-13; for a single node's
+// value by one end of 32 x 4 x 4 elements 1.5e-15 of the largest datum against 1.3e-16, and at the far end 1e-14
+// of the datum itself against 3e-16.)
 // (A node whose coordinate is its own mirror image, the middle one of an odd count,
 // is met twice by the group; its weight is halved per such axis.)
 //
@@ -48,7 +51,7 @@
 // the padded width on the matrix unit); the FP64 vector and matrix instructions do not
 // overlap, so the sum of the two bounds it.
 // Tried: 48 and 64 sources a tile (one wave per SIMD: 9.7 and 28 ms), K of the next step formed
-// between the matrix instructions (no faster: 6.5 ms).
+// between the matrix instructions (no faster).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -65,10 +68,10 @@ namespace {
 
 constexpr int QUAD_BLOCK = 256;    // threads per work-group
 constexpr int QUAD_VEC = 4;        // widest source tile of the vector kernel
-// Source tile for `left` more sources, at most rmax.  Up to 4 go to the vector kernel (1.63 to 1.95 ms
-// on 16^3 elements, p = 4, against 2.8 ms for a matrix tile of 16; its records then fill the SGPRs), more
-// to the narrowest matrix tile that holds them (17..20 sources: 4.5 ms in a tile of 32, 4.7 ms in 16
-// and a vector pass).
+// Source tile for `left` more sources, at most rmax.  Up to 4 go to the vector kernel (1.3 to 1.6 ms on 16^3
+// elements, p = 4, against 2.6 ms for a matrix tile of 16; its records then fill the SGPRs), more to the
+// narrowest matrix tile that holds them (17 to 20 sources: 4.30 ms in a tile of 32; 16 and a vector pass of 1, 2
+// or 4 would take 4.06, 4.18 and 4.32).
 constexpr int quad_tile(int left, int rmax) {
     if (left > 16 && rmax >= 32) return 32;
     if (left > QUAD_VEC && rmax >= 16) return 16;

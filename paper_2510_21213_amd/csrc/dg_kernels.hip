@@ -714,8 +714,10 @@ __device__ __forceinline__ void pair_row(const SlabCoef<T, N, GL>& c, const T* s
 // x (and y) terms.  The lanes of a wave write a layer by nodes (i, j) of elements and read it by rows,
 // RS apart, or columns; with the strides left at the widths of the rows the accesses of a p = 4 layer took
 // 3.7 times the cycles they need (SQ_LDS_BANK_CONFLICT; the LDS was busy 45% of the FP32 smoothing
-// step's time).  The paddings are the least-conflict ones of a count over all accesses of a layer, 32
-// banks of 4 bytes, within the LDS that the registers' occupancy leaves.  Step of 128 right-hand sides of
+// step's time).  The paddings are the least-conflict ones of a count, within the LDS that the registers'
+// occupancy leaves: for each access of a layer (a column's and the halo's values written, x and y pair rows
+// read, their results written and read back) and each half of a wave, the most distinct values that fall on one
+// of 32 banks (a value a bank, for FP64 too), summed over strides up to 11 values longer and planes up to 14.  Step of 128 right-hand sides of
 // 32^3 elements, BF16 fields: conflict cycles 497 -> 210 a wave, 1473 -> 1449 us; whole solves 1 to 3%.
 // PLAIN: no padding (the restriction steps of degree 4, whose third array would cost them a work-group
 // per CU: 1.51 ms against 1.44).
@@ -1513,8 +1515,8 @@ struct SlabGeom {
 // and 2048 16^3 x 4 takes 5.42, 5.08, 5.04 and 5.16 ms, and 16^3 x 36 with one layer a chunk 20.5
 // against 16.9.  Solves that run at the same time fill the GPU together: two lanes of a mesh overlap
 // only in part and keep the whole target each (10x14x12 p = 5 and 8^3 Gauss-Legendre cases: 6.87 and
-// 10.9 ms, 7.70 and 12.5 at 256), six meshes of 4^3 to 14^3 at once (96 right-hand sides) take 28.3 ms
-// at 576 and 28.0 at 256 and with full chunks.
+// 10.9 ms, 7.70 and 12.5 at 256); three meshes of 8^3, 12^3 and 16^3 elements on two lanes each (six solves at
+// once, 96 right-hand sides) take 27.7 ms at 576 and 27.3 with this rule (192), at 256 and with full chunks.
 int slab_wgs(int jobs) { return std::min(576, 1152 / std::max(1, jobs)); }
 
 template <typename T>
