@@ -65,13 +65,15 @@ BLOCK_END = re.compile(r"s_(cbranch|branch|endpgm|setpc|barrier|and_saveexec|mov
 
 
 def early_copies(lines):
-    """Vector instructions between the target of an s_cbranch_execz and the instruction that restores the lanes
-    there: (function, address, instruction)."""
+    """Vector instructions between the target of an s_cbranch_execz, or a loop's end (s_cbranch_execnz
+    backwards), and the
+    instruction that restores the lanes there: (function, address, instruction)."""
     code, func, found = [], "", []
 
     def check():
         targets = {a + 4 + 4 * (w & 0xffff if not w & 0x8000 else (w & 0xffff) - 0x10000)
                    for a, w, t in code if t.startswith("s_cbranch_execz")}
+        targets |= {a + 4 for a, w, t in code if t.startswith("s_cbranch_execnz") and w & 0x8000}
         pending = None
         for a, _, t in code:
             if a in targets:
